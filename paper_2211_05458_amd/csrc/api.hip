@@ -53,6 +53,7 @@ struct fp_ctx {
   void* tasks = nullptr;
   double* trk_x = nullptr;
   uint8_t* trk_m = nullptr;
+  float* trk_s = nullptr;
   bool tasks_valid = false;
   // fluid
   Fluid fl{};
@@ -241,10 +242,10 @@ void particle_offsets(int64_t cap, int64_t* off, size_t* total) {
 
 
 struct Layout {
-  size_t X, faces, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
+  size_t X, faces, fext, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
       mlp_flag, mlp_h1, mlp_ctr, mlp_w, mlp_adam, mlp_order, mlp_bloss, dl_count, dl_start, dl_list, stats,
       sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, mlp_grad, tcount, tstart, tasks, qcnt,
-      strag, trk_p, trk_x, trk_m, mlp_guess, part[2], total;
+      strag, trk_p, trk_x, trk_m, trk_s, mlp_guess, part[2], total;
   size_t part_bytes;
 };
 
@@ -255,6 +256,7 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   size_t E = c->E, ng3 = (size_t)c->ng * c->ng * c->ng, n3 = (size_t)c->n * c->n * c->n;
   L.X = take(E * ng3 * 3 * 8);
   L.faces = take(E * 6 * sizeof(FaceRec));
+  L.fext = take(E * 6 * sizeof(FaceExt));
   L.cp = take(E * 6 * c->ng * c->ng * 3 * 8);
   L.hE = take(E * 8);
   L.xnode = take(E * n3 * 3 * 8);
@@ -300,6 +302,7 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   L.trk_p = take(pc1 * 4);
   L.trk_x = take(pc1 * 3 * 8);
   L.trk_m = take(pc1);
+  L.trk_s = take(pc1 * 3 * 4);
   L.mlp_guess = take(pc1 * 3 * 4);
   {
     int64_t off[10];
@@ -708,6 +711,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   m.E = c->E; m.ng = c->ng; m.n = c->n; m.n_geo = c->n_geo;
   m.X = (const double*)(b + L.X);
   m.faces = (const FaceRec*)(b + L.faces);
+  m.fext = (const FaceExt*)(b + L.fext);
   m.cp = (const double*)(b + L.cp);
   m.hE = (const double*)(b + L.hE);
   m.xnode = (const double*)(b + L.xnode);
@@ -753,6 +757,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   c->trk_p = (int32_t*)(b + L.trk_p);
   c->trk_x = (double*)(b + L.trk_x);
   c->trk_m = (uint8_t*)(b + L.trk_m);
+  c->trk_s = (float*)(b + L.trk_s);
   c->tasks_valid = false;
   c->part0 = b + L.part[0];
   c->P[0] = carve(b + L.part[0], c->cap);
@@ -772,7 +777,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   HIPCHK(c, hipMemsetAsync(c->scratch_i32, 0, 64, s));
   HIPCHK(c, launch_face_setup(m, m.X, (const int32_t*)(b + L.nbr_elem), (const int32_t*)(b + L.nbr_face),
                               (const int8_t*)(b + L.bc), (const double*)(b + L.shift), c->Minv.data(),
-                              (FaceRec*)(b + L.faces), (double*)(b + L.cp), s));
+                              (FaceRec*)(b + L.faces), (FaceExt*)(b + L.fext), (double*)(b + L.cp), s));
   HIPCHK(c, launch_nodes(m, (double*)(b + L.xnode), (double*)(b + L.vol), (double*)(b + L.hE), (double*)(b + L.nbox),
                          (double*)(b + L.gxi), c->scratch_i32, (unsigned long long*)(b + L.scratch + 8), s));
   int32_t bad = 0;
@@ -938,6 +943,7 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
       Lc.trk_p = c->trk_p;
       Lc.trk_x = c->trk_x;
       Lc.trk_m = c->trk_m;
+      Lc.trk_s = c->trk_s;
       Lc.stats = c->stats;
       if (c->timing)
         for (int k = 0; k < (sp.mlp_guess ? 8 : 6); ++k) Lc.ev[k] = take_event(c);

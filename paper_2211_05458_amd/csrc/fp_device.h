@@ -887,6 +887,112 @@ __device__ inline void face_setup(const double* __restrict__ Xe, int f, const do
   F.type = (planar && bilin && tw <= tol) ? FACE_PLANAR : (bilin ? FACE_BILINEAR : FACE_CURVED);
 }
 
+// Bounds of a face for face_root (see FaceExt) from its Bernstein control
+// points: the tangents and second derivatives of the patch lie in the convex
+// hulls of the control vectors of its hodographs.
+template <int NG>
+__device__ inline void face_bounds(const double* __restrict__ cp, const FaceRec& F, FaceExt& X) {
+  constexpr int D = NG - 1;
+  auto P = [&](int k, int i, int q) { return cp[(k * NG + i) * 3 + q]; };
+  double T[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, R[2][3] = {{0, 0, 0}, {0, 0, 0}};
+  for (int dir = 0; dir < 2; ++dir)
+    for (int k = 0; k < NG; ++k)
+      for (int i = 0; i < D; ++i) {
+        double d[3];
+        for (int q = 0; q < 3; ++q) d[q] = 0.5 * D * (dir ? P(i + 1, k, q) - P(i, k, q) : P(k, i + 1, q) - P(k, i, q));
+        for (int a = 0; a < 3; ++a) {
+          R[dir][a] += d[a];
+          for (int b = 0; b < 3; ++b) T[a][b] += d[a] * d[b];
+        }
+      }
+  // least squares over the control vectors: B T = R, regularised along the
+  // normal of a plane face
+  const double reg = 1e-6 * (T[0][0] + T[1][1] + T[2][2]);
+  for (int a = 0; a < 3; ++a) T[a][a] += reg;
+  const double id = 1.0 / det3(T);
+  double Ti[3][3];
+  for (int a = 0; a < 3; ++a)
+    for (int b = 0; b < 3; ++b) {
+      const int a1 = (a + 1) % 3, a2 = (a + 2) % 3, b1 = (b + 1) % 3, b2 = (b + 2) % 3;
+      Ti[b][a] = (T[a1][b1] * T[a2][b2] - T[a1][b2] * T[a2][b1]) * id;
+    }
+  double B[2][3];
+  for (int r = 0; r < 2; ++r)
+    for (int b = 0; b < 3; ++b) {
+      B[r][b] = R[r][0] * Ti[0][b] + R[r][1] * Ti[1][b] + R[r][2] * Ti[2][b];
+      X.B[r * 3 + b] = (float)B[r][b];
+      B[r][b] = (double)X.B[r * 3 + b];   // the bounds below hold for the stored matrix
+    }
+  double eps2 = 0.0, c2 = 0.0, cc[3] = {0, 0, 0};
+  for (int dir = 0; dir < 2; ++dir) {
+    double mx = 0.0;
+    for (int k = 0; k < NG; ++k)
+      for (int i = 0; i < D; ++i) {
+        double d[3];
+        for (int q = 0; q < 3; ++q) d[q] = 0.5 * D * (dir ? P(i + 1, k, q) - P(i, k, q) : P(k, i + 1, q) - P(k, i, q));
+        const double r0 = dot3(B[0], d) - (dir ? 0.0 : 1.0), r1 = dot3(B[1], d) - (dir ? 1.0 : 0.0);
+        mx = fmax(mx, r0 * r0 + r1 * r1);
+      }
+    eps2 += mx;
+  }
+  // second derivatives: uu, vv (weight 1), uv (weight 2 in the squared norm)
+  for (int kind = 0; kind < 3; ++kind) {
+    double mx = 0.0, mc[3] = {0, 0, 0};
+    const int nk = kind == 0 ? NG : kind == 1 ? D - 1 : D, ni = kind == 0 ? D - 1 : kind == 1 ? NG : D;
+    for (int k = 0; k < nk; ++k)
+      for (int i = 0; i < ni; ++i) {
+        double d[3];
+        for (int q = 0; q < 3; ++q)
+          d[q] = kind == 0   ? 0.25 * D * (D - 1) * (P(k, i + 2, q) - 2.0 * P(k, i + 1, q) + P(k, i, q))
+                 : kind == 1 ? 0.25 * D * (D - 1) * (P(k + 2, i, q) - 2.0 * P(k + 1, i, q) + P(k, i, q))
+                             : 0.25 * D * D * (P(k + 1, i + 1, q) - P(k + 1, i, q) - P(k, i + 1, q) + P(k, i, q));
+        mx = fmax(mx, dot3(d, d));
+        const double a[3] = {dot3(d, F.nrm), dot3(d, F.e1), dot3(d, F.e2)};
+        for (int q = 0; q < 3; ++q) mc[q] = fmax(mc[q], a[q] * a[q]);
+      }
+    const double w = kind == 2 ? 2.0 : 1.0;
+    c2 += w * mx;
+    for (int q = 0; q < 3; ++q) cc[q] += w * mc[q];
+  }
+  const double eps = 1.03 * sqrt(eps2) + 1e-4;
+  X.inv1e = eps < 0.95 ? (float)(1.001 / (1.0 - eps)) : 0.0f;
+  // an absolute floor of 1e-12 diameters keeps the bounds above rounding on plane faces
+  const double fl = 1e-12 * F.diam;
+  X.c2 = (float)(1.03 * sqrt(c2) + fl);
+  X.cn = (float)(1.03 * sqrt(cc[0]) + fl);
+  X.c1 = (float)(1.03 * sqrt(cc[1]) + fl);
+  X.c2f = (float)(1.03 * sqrt(cc[2]) + fl);
+}
+
+// how the face parameters of the neighbour across face f of element e follow
+// from those of f (FaceExt::orient), from the four corners; 8 if they do not match
+template <int NG>
+__device__ inline int face_orientation(const double* __restrict__ X, int e, int f, const FaceRec& F) {
+  constexpr int D = NG - 1;
+  auto corner = [&](int el, int face, int a, int b, double* p) {
+    const int d = face / 2, ax = (d == 0) ? 1 : 0, bx = (d == 2) ? 1 : 2;
+    int idx[3];
+    idx[d] = (face & 1) ? D : 0; idx[ax] = a * D; idx[bx] = b * D;
+    const double* Q = X + ((size_t)el * NG * NG * NG + (idx[2] * NG + idx[1]) * NG + idx[0]) * 3;
+    for (int q = 0; q < 3; ++q) p[q] = Q[q];
+  };
+  const double tol = 1e-9 * F.diam;
+  for (int code = 0; code < 8; ++code) {
+    bool ok = true;
+    for (int c = 0; c < 4 && ok; ++c) {
+      const int a = c & 1, b = c >> 1;
+      const int s0 = (code & 1) ? b : a, s1 = (code & 1) ? a : b;
+      double p[3], r[3];
+      corner(e, f, a, b, p);
+      corner(F.nbr_elem, F.nbr_face, (code & 2) ? 1 - s0 : s0, (code & 4) ? 1 - s1 : s1, r);
+      for (int q = 0; q < 3; ++q)
+        if (!(fabs(p[q] + (F.bc == BC_PERIODIC ? F.shift[q] : 0.0) - r[q]) <= tol)) ok = false;
+    }
+    if (ok) return code;
+  }
+  return 8;
+}
+
 // Local faces that a segment of squared length L2 starting at reference
 // point xi of element e could reach (bit f; face f lies at xi_{f/2} = -1 for
 // even f, +1 for odd f): along a path inside the element xi_i changes by at
@@ -904,6 +1010,15 @@ __device__ __forceinline__ unsigned reachable_faces(const MeshView& m, int e, co
     if (!(rp > 0.0 && gl2 < rp * rp)) mask |= 1u << (2 * i + 1);
   }
   return mask;
+}
+
+// local faces of an element that are not internal (wall, open, periodic,
+// mortar): their crossings cannot be repaired by following xi to a neighbour
+__device__ __forceinline__ unsigned boundary_faces(const FaceRec* __restrict__ Fe) {
+  unsigned b = 0;
+#pragma unroll
+  for (int f = 0; f < 6; ++f) b |= (Fe[f].bc != BC_INTERNAL ? 1u : 0u) << f;
+  return b;
 }
 
 // Refinement of reachable_faces for a segment x -> xe from reference point xi
@@ -1058,592 +1173,721 @@ __device__ __forceinline__ void bern(double t, double* B, double* dB) {
   }
 }
 
+__device__ constexpr double kBinom[7][7] = {{1, 0, 0, 0, 0, 0, 0}, {1, 1, 0, 0, 0, 0, 0}, {1, 2, 1, 0, 0, 0, 0},
+                                            {1, 3, 3, 1, 0, 0, 0}, {1, 4, 6, 4, 1, 0, 0}, {1, 5, 10, 10, 5, 1, 0},
+                                            {1, 6, 15, 20, 15, 6, 1}};
+
+// Position and tangents of a face at (u, v): the rows along u by Bernstein
+// weights, the sum over the rows in the scaled Horner form (non-negative terms
+// inside the face).  The control points are read anew in each call: kept in
+// registers over Newton's iterations (150 of them for degree 4, 294 for degree
+// 6) they would leave one wavefront per SIMD.
 template <int NG>
-__device__ inline void bezier_eval(const double* __restrict__ cp, double u, double v, double* p, double* pu,
-                                   double* pv) {
+__device__ __forceinline__ void face_eval(const double* __restrict__ cp, double u, double v, double* p, double* pu,
+                                          double* pv) {
   constexpr int D = NG - 1;
-  double Bu[NG], Bv[NG], dBu[NG], dBv[NG];
+  double Bu[NG], dBu[NG];
   bern<D>(0.5 * (u + 1.0), Bu, dBu);
-  bern<D>(0.5 * (v + 1.0), Bv, dBv);
-  for (int q = 0; q < 3; ++q) { p[q] = 0.0; if (pu) { pu[q] = 0.0; pv[q] = 0.0; } }
-#pragma unroll 1
-  for (int k = 0; k < NG; ++k)
-#pragma unroll 1
-    for (int mm = 0; mm < NG; ++mm) {
-      const double* P = cp + (k * NG + mm) * 3;
-      double w = Bu[mm] * Bv[k];
+  const double b = 0.5 * (v + 1.0), w = 0.5 * (1.0 - v);
+  double vk = 1.0, vd = 0.0;   // b^k, k b^(k-1)
+  asm volatile("" : "+v"(cp));
+#pragma unroll
+  for (int q = 0; q < 3; ++q) p[q] = pu[q] = pv[q] = 0.0;
+  constexpr int kUnroll = NG <= 3 ? NG : 2;
+#pragma unroll kUnroll
+  for (int k = 0; k < NG; ++k) {
+    double r[3] = {0.0, 0.0, 0.0}, ru[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
       for (int q = 0; q < 3; ++q) {
-        p[q] += P[q] * w;
-        if (pu) {
-          pu[q] += P[q] * 0.5 * dBu[mm] * Bv[k];
-          pv[q] += P[q] * 0.5 * Bu[mm] * dBv[k];
-        }
+        const double c = cp[(k * NG + i) * 3 + q];
+        r[q] += c * Bu[i];
+        ru[q] += c * dBu[i];
       }
+    const double f = kBinom[D][k] * vk, fd = kBinom[D][k] * vd;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      pv[q] = pv[q] * w - p[q] + fd * r[q];
+      p[q] = p[q] * w + f * r[q];
+      pu[q] = pu[q] * w + f * ru[q];
     }
+    vd = vd * b + vk;
+    vk *= b;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    pu[q] *= 0.5;
+    pv[q] *= 0.5;
+  }
 }
 
-// restrict a stride-s list of NG Bezier coefficients to [a, b]
+// Where on a face the points of the segment xs + [0, L] t can lie, seen from
+// the face point w0 = (u, v) with position p and tangents J = (pu, pv), r = p - xs:
+// with c2 >= |d2p|, every face point p(w) = q on the segment satisfies
+//   |w - w0 - J+ (q - p)| <= h,  h = c2 rho^2 / (2 sigma),  |w - w0| <= rho,
+// J+ the pseudo-inverse and sigma the smallest singular value of J, q between
+// the displacements lo and hi.  rho is the smallest of the caller's `reach`,
+// the face's B bound and the small branch of rho = a + c2 rho^2 / (2 sigma),
+// a the largest |J+ (q - p)|, where the other bounds exclude the large one;
+// [lo, hi] follows from |q - p| <= rho (largest singular value + c2 rho / 2).
+// false: no such point.
+struct FaceRange {
+  double rho, h, lo, hi;
+  double ws[2], we[2];   // J+ (q - p) at lo and hi
+};
+
+__device__ __forceinline__ bool face_range(const FaceExt& X, const double* r, const double* t, double L,
+                                           const double* pu, const double* pv, double reach, FaceRange& R) {
+  double rho = reach;
+  const double c2 = X.c2;
+  if (X.inv1e > 0.0f) {
+    const double a0 = X.B[0] * r[0] + X.B[1] * r[1] + X.B[2] * r[2], a1 = X.B[3] * r[0] + X.B[4] * r[1] + X.B[5] * r[2];
+    const double b0 = L * (X.B[0] * t[0] + X.B[1] * t[1] + X.B[2] * t[2]) - a0;
+    const double b1 = L * (X.B[3] * t[0] + X.B[4] * t[1] + X.B[5] * t[2]) - a1;
+    rho = fmin(rho, sqrt(fmax(a0 * a0 + a1 * a1, b0 * b0 + b1 * b1)) * (double)X.inv1e);
+  }
+  const double guu = dot3(pu, pu), guv = dot3(pu, pv), gvv = dot3(pv, pv);
+  const double gm = 0.5 * (guu + gvv), gd = sqrt(0.25 * (guu - gvv) * (guu - gvv) + guv * guv);
+  const double al = dot3(r, t), ext = rho * (1.001 * sqrt(gm + gd) + 0.505 * c2 * rho) + 1e-9 * L;
+  R.lo = fmax(0.0, al - ext);
+  R.hi = fmin(L, al + ext);
+  const double ig = 1.0 / (guu * gvv - guv * guv);
+  const double ru = dot3(pu, r), rv = dot3(pv, r), tu = dot3(pu, t), tv = dot3(pv, t);
+  const double w0[2] = {-(gvv * ru - guv * rv) * ig, -(guu * rv - guv * ru) * ig};
+  const double wt[2] = {(gvv * tu - guv * tv) * ig, (guu * tv - guv * tu) * ig};
+  double a2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    R.ws[k] = w0[k] + R.lo * wt[k];
+    R.we[k] = w0[k] + R.hi * wt[k];
+  }
+  a2 = fmax(R.ws[0] * R.ws[0] + R.ws[1] * R.ws[1], R.we[0] * R.we[0] + R.we[1] * R.we[1]);
+  const double a = sqrt(a2) * 1.001 + 1e-9, b = 0.505 * c2 / sqrt(gm - gd);
+  const double disc = 1.0 - 4.0 * a * b;
+  if (disc > 0.0) {
+    const double sq = 1.0 + sqrt(disc);
+    if (2.0 * b * rho < 0.999 * sq) rho = fmin(rho, 2.0 * a / sq);
+  }
+  R.rho = rho + 1e-9;
+  R.h = b * R.rho * R.rho + 1e-9;   // NaN or inf (degenerate tangents) fails every test on it
+  return R.lo <= R.hi;
+}
+
+// Contraction bound of the projected Newton map at w0 (A the inverse of the
+// projected tangents): A (P(w) - P(w0)) = (I + E)(w - w0) with
+// |E| <= rho / 2 |A Pi d2p|, the returned value, for |w - w0| <= rho.
+__device__ __forceinline__ double root_contraction(const FaceRec& F, const FaceExt& X, const double* n1,
+                                                   const double* n2, const double A[4], double rho) {
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double* a = k == 0 ? F.nrm : k == 1 ? F.e1 : F.e2;
+    const double c = k == 0 ? X.cn : k == 1 ? X.c1 : X.c2f;
+    const double q1 = dot3(a, n1), q2 = dot3(a, n2);
+    const double r0 = A[0] * q1 + A[1] * q2, r1 = A[2] * q1 + A[3] * q2;
+    s += c * sqrt(r0 * r0 + r1 * r1);
+  }
+  return 0.5 * rho * s;
+}
+
+enum { ROOT_NONE = 0, ROOT_ONE = 1, ROOT_NEAR = 2, ROOT_OPEN = 3 };
+constexpr double kMaxContraction = 0.95;   // the bounds it is compared with hold a margin of 3 % of their own
+
+// Intersection of the segment xs + [0, L] t with the part
+// |u - box[0]| <= box[2], |v - box[1]| <= box[3] of a curved face by Newton on
+// the two plane distances, from (u, v) and kept to that part: ROOT_ONE with the
+// root's (u, v), displacement al and t . (pu x pv) if the contraction bound
+// shows it to be the only one there on the segment, ROOT_NEAR with a root that
+// is the only one within off of it in u and v, ROOT_NONE if the bounds show
+// that the segment meets no point of that part, else ROOT_OPEN with the last
+// iterate (off: its squared distance from the line).  ROOT_NEAR and ROOT_OPEN
+// cut the box to where points of the segment can lie; path: the image
+// (path[0], path[1]) + displacement (path[2], path[3]) of the segment in the
+// face's tangent plane there.  (us, vs), dr: with `local`, no point further
+// than dr from (us, vs) counts; sole is cleared where a root exists that may
+// not be the only one further out.
 template <int NG>
-__device__ inline void restrict1(double* c, int s, double a, double b) {
-  double tmp[NG], left[NG];
-#pragma unroll
-  for (int i = 0; i < NG; ++i) tmp[i] = c[i * s];
-  left[0] = tmp[0];
-#pragma unroll
-  for (int r = 1; r < NG; ++r) {
-#pragma unroll
-    for (int i = 0; i < NG - r; ++i) tmp[i] = (1.0 - b) * tmp[i] + b * tmp[i + 1];
-    left[r] = tmp[0];
-  }
-  if (b <= 0.0) {
-#pragma unroll
-    for (int i = 0; i < NG; ++i) c[i * s] = left[0];
-    return;
-  }
-  double t = a / b;
-#pragma unroll
-  for (int i = 0; i < NG; ++i) tmp[i] = left[i];
-  c[(NG - 1) * s] = tmp[NG - 1];
-#pragma unroll
-  for (int r = 1; r < NG; ++r) {
-#pragma unroll
-    for (int i = 0; i < NG - r; ++i) tmp[i] = (1.0 - t) * tmp[i] + t * tmp[i + 1];
-    c[(NG - 1 - r) * s] = tmp[NG - 1 - r];
-  }
-}
-
-// q[m][k][C] with m along u, k along v; restrict direction dir to [a, b]
-template <int NG, int C>
-__device__ inline void patch_restrict(double* q, int dir, double a, double b) {
-#pragma unroll
-  for (int k = 0; k < NG; ++k)
-#pragma unroll
-    for (int co = 0; co < C; ++co) {
-      if (dir == 0) restrict1<NG>(q + k * C + co, NG * C, a, b);   // along m
-      else restrict1<NG>(q + k * NG * C + co, C, a, b);            // along k
-    }
-}
-
-// t-extent of H intersected with {y >= c} (ge) or {y <= c}, where H is the
-// convex hull of the columns t_i = i/(NP-1), y in [lo_i, hi_i].  Only the
-// column maxima (ge) or minima bound that intersection; its extent is spanned
-// by the columns inside the half-plane and by the crossings of y = c on the
-// segments between a column inside and a column outside (every such crossing
-// lies in H, and the hull edge that leaves the half-plane is one of them).
-template <int NP>
-__device__ __forceinline__ bool half_extent(const double* lo, const double* hi, double c, bool ge, double& a,
-                                            double& b) {
-  const double* y = ge ? hi : lo;
-  const double step = 1.0 / (NP - 1);
-  double tmin = 1e300, tmax = -1e300;
-  bool in[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    in[i] = ge ? (y[i] >= c) : (y[i] <= c);
-    if (in[i]) { tmin = fmin(tmin, i * step); tmax = fmax(tmax, i * step); }
-  }
-#pragma unroll
-  for (int i = 0; i < NP; ++i)
-#pragma unroll
-    for (int j = i + 1; j < NP; ++j)
-      if (in[i] != in[j]) {
-        double t = (i + (j - i) * ((c - y[i]) / (y[j] - y[i]))) * step;
-        tmin = fmin(tmin, t);
-        tmax = fmax(tmax, t);
-      }
-  a = tmin;
-  b = tmax;
-  return tmin <= tmax;
-}
-
-// Clip direction dir (0: u, 1: v) of the projected patch q[m][k][3] (signed
-// distances to the two planes that contain the ray in components 0 and 1):
-// Bezier clipping against the line through the origin that runs along the
-// other parameter direction.  The convex-hull property of the Bernstein form
-// keeps every root.
-template <int NG>
-__device__ inline bool clip_dir(const double* q, int dir, double amin, double amax, double& a, double& b) {
-  constexpr int N = NG - 1;
-#define QQ(m, k, c) q[((m) * NG + (k)) * 3 + (c)]
-  double L0, L1;
-  if (dir == 0) {
-    L0 = (QQ(0, N, 0) - QQ(0, 0, 0)) + (QQ(N, N, 0) - QQ(N, 0, 0));
-    L1 = (QQ(0, N, 1) - QQ(0, 0, 1)) + (QQ(N, N, 1) - QQ(N, 0, 1));
-  } else {
-    L0 = (QQ(N, 0, 0) - QQ(0, 0, 0)) + (QQ(N, N, 0) - QQ(0, N, 0));
-    L1 = (QQ(N, 0, 1) - QQ(0, 0, 1)) + (QQ(N, N, 1) - QQ(0, N, 1));
-  }
-  double ll = sqrt(L0 * L0 + L1 * L1);
-  if (ll == 0.0) {
-    double K0, K1;
-    if (dir == 0) {
-      K0 = (QQ(N, 0, 0) - QQ(0, 0, 0)) + (QQ(N, N, 0) - QQ(0, N, 0));
-      K1 = (QQ(N, 0, 1) - QQ(0, 0, 1)) + (QQ(N, N, 1) - QQ(0, N, 1));
-    } else {
-      K0 = (QQ(0, N, 0) - QQ(0, 0, 0)) + (QQ(N, N, 0) - QQ(N, 0, 0));
-      K1 = (QQ(0, N, 1) - QQ(0, 0, 1)) + (QQ(N, N, 1) - QQ(N, 0, 1));
-    }
-    L0 = -K1; L1 = K0;
-    ll = sqrt(L0 * L0 + L1 * L1);
-    if (ll == 0.0) { L0 = 1.0; L1 = 0.0; ll = 1.0; }
-  }
-  double nx = -L1 / ll, ny = L0 / ll;
-  double dlo[NG], dhi[NG];
-#pragma unroll
-  for (int i = 0; i < NG; ++i) {
-    double mn = 1e300, mx = -1e300;
-#pragma unroll
-    for (int k = 0; k < NG; ++k) {
-      double dist = (dir == 0) ? nx * QQ(i, k, 0) + ny * QQ(i, k, 1) : nx * QQ(k, i, 0) + ny * QQ(k, i, 1);
-      mn = fmin(mn, dist);
-      mx = fmax(mx, dist);
-    }
-    dlo[i] = mn;
-    dhi[i] = mx;
-  }
-#undef QQ
-  double a1, b1, a2, b2;
-  if (!half_extent<NG>(dlo, dhi, 0.0, true, a1, b1)) return false;
-  if (!half_extent<NG>(dlo, dhi, 0.0, false, a2, b2)) return false;
-  double lo = fmax(a1, a2), hi = fmin(b1, b2);
-  if (lo > hi) return false;
-  // the displacement band amin <= alpha <= amax (component 2), on the same
-  // convex hull of the rows' ranges
-#pragma unroll
-  for (int i = 0; i < NG; ++i) {
-    double mn = 1e300, mx = -1e300;
-#pragma unroll
-    for (int k = 0; k < NG; ++k) {
-      double al = (dir == 0) ? q[(i * NG + k) * 3 + 2] : q[(k * NG + i) * 3 + 2];
-      mn = fmin(mn, al);
-      mx = fmax(mx, al);
-    }
-    dlo[i] = mn;
-    dhi[i] = mx;
-  }
-  if (!half_extent<NG>(dlo, dhi, amin, true, a1, b1)) return false;
-  if (!half_extent<NG>(dlo, dhi, amax, false, a2, b2)) return false;
-  lo = fmax(lo, fmax(a1, a2));
-  hi = fmin(hi, fmin(b1, b2));
-  if (lo > hi) return false;
-  a = fmax(0.0, lo - kClipPad);
-  b = fmin(1.0, hi + kClipPad);
-  return true;
-}
-
-// projected control points of the whole face: distances to the planes n1, n2
-// (components 0, 1) and displacement along t (component 2), [m along u][k along v]
-template <int NG>
-__device__ __forceinline__ void project_face(const double* __restrict__ cp, const double* x0, const double* t,
-                                             const double* n1, const double* n2, double* q) {
-#pragma unroll
-  for (int k = 0; k < NG; ++k)
-#pragma unroll
-    for (int mm = 0; mm < NG; ++mm) {
-      const double* P = cp + (k * NG + mm) * 3;
-      double r[3] = {P[0] - x0[0], P[1] - x0[1], P[2] - x0[2]};
-      q[(mm * NG + k) * 3 + 0] = dot3(r, n1);
-      q[(mm * NG + k) * 3 + 1] = dot3(r, n2);
-      q[(mm * NG + k) * 3 + 2] = dot3(r, t);
-    }
-}
-
-// the displacement of every point of the (sub-)patch lies outside [amin, amax]
-template <int NG>
-__device__ __forceinline__ bool outside_band(const double* q, double amin, double amax) {
-  double lo = 1e300, hi = -1e300;
-#pragma unroll
-  for (int i = 0; i < NG * NG; ++i) {
-    lo = fmin(lo, q[i * 3 + 2]);
-    hi = fmax(hi, q[i * 3 + 2]);
-  }
-  return hi < amin || lo > amax;
-}
-
-// Physical-space tracking of the queued straight stage segments xs -> xe
-// (Sec. 3.2.3): smallest alpha in (1e-12 h_e, remaining length] with (u, v) in
-// [-1,1]^2, ties to the lowest local face; hand-off, periodic shift, specular
-// reflection (Sec. 2.4) of the remaining displacement, v and the stage
-// registers; open boundaries end the particle.
-//
-// Written as a per-lane state machine: one loop iteration advances a lane by
-// one step of its own work (next candidate face, pop of a clipping box, one
-// Bezier-clipping iteration, end of a leg), so the lanes of a wavefront that
-// test different faces, need different iteration counts or cross different
-// numbers of faces all share the clipping iteration that dominates the cost.
-// A lane whose segment is done takes the next one from the queue (one atomic
-// per wavefront and iteration for all its idle lanes), so the lanes stay busy
-// until the queue is drained instead of each wavefront waiting for its
-// slowest segment.  The results do not depend on the order.
-__device__ __forceinline__ int lane_rank64(unsigned long long mask) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-}
-
-template <int NG, bool MORT>
-__device__ void track_queue(const MeshView& m, const Particles& P, const int32_t* __restrict__ trk_p,
-                            const double* __restrict__ trk_x, const uint8_t* __restrict__ trk_m, int32_t* head,
-                            int64_t nq, int max_cross, int& ncross, int& nhits) {
-  constexpr double kBoxTol = 1e-7;
-  // Bezier clipping contracts a box around a simple root quadratically; once
-  // both sides are below kNewtonBox and the last iteration cut each of them to
-  // at most kQuadRatio, the box holds one transversal root and the 2-D Newton
-  // below reaches it in three steps (a double root, where the clipping only
-  // contracts linearly, keeps clipping down to kBoxTol)
-  constexpr double kNewtonBox = 1e-3, kQuadRatio = 0.25;
-  enum { NEW_LEG, NEXT_FACE, POP, CLIP, LEG_END, MORT_FACE, MORT_END, DONE };
-  // idle lanes take new segments once at least kRefill of them wait (one
-  // atomic on the queue head and one pass of the refill code per batch):
-  // measured per-stage tracking, degree 4 with 1.1e6 segments 6.6 -> 5.2 ms
-  // at 32 (8: 6.3, 16: 5.6), degree 6 with 1.3e6 segments 23.7 -> 22.7 ms at
-  // 8 (16: 22.9, 32: 23.8); a queue of 4e4 segments loses 0.01 ms at either
-  constexpr int kRefill = NG >= 7 ? 8 : 32;
-  const int64_t cap = P.cap;
-  // the lane's segment: particle, element at the start, wall hits, crossings
-  int64_t p = -1;
-  int e = 0, e0 = 0, hits = 0, nseg = 0;
-  int8_t status = ACTIVE;
-  unsigned reach = 0x3Fu;
-  double xe[3] = {0, 0, 0}, v[3] = {0, 0, 0}, kx[3] = {0, 0, 0}, kv[3] = {0, 0, 0};
-  double xs[3] = {0, 0, 0};
-  // excl: planar face just entered through (no further root possible);
-  // entry: non-planar face just entered through, whose root at the entry point
-  // (alpha ~ 0, error growing like 1/sin(incidence)) is ignored below
-  // kEntryRel * face diameter
-  int excl = -1, entry = -1, count = 0;
-  double t[3] = {0, 0, 0}, n1[3] = {0, 0, 0}, n2[3] = {0, 0, 0}, L = 0.0, eps = 0.0;
-  double best = 1e300, bu = 0.0, bv = 0.0, amin = 0.0, bmin = 0.0, bmax = 0.0;
-  int bf = -1, f = 0;
-  int fl = 0;   // local index of the face under test (its outward-normal sign)
-  // non-conforming side: mortar index, cursor over its small faces, the
-  // big-face crossing and the small-face root nearest it
-  int mort = -1, mj = 0, mbig = -1, ms = -1, mf = -1, mse = -1, msf = -1;
-  double astar = 0.0, mbd = 1e300, msa = 0.0;
-  const double* cpf = m.cp;
-  double stk[kClipStack][4];
-  int sp = 0, budget = 0;
-  double u0 = 0.0, u1 = 1.0, v0 = 0.0, v1 = 1.0;
-  double q[NG * NG * 3];
-  // a root counts if it lies in (amin, L], on the face, and the path leaves
-  // the element there: tn = t . outward normal > 0 (a root where the path
-  // enters, at a tangential touch or the entry point, is not a crossing)
-  auto consider = [&](double a, double uu, double vv, double tn) {
-    if (fabs(uu) > 1.0 + kUVEps || fabs(vv) > 1.0 + kUVEps) return;
-    if (MORT && mort >= 0) {
-      // small face of a mortar: a root where the path enters the small element
-      // (where the inverted path leaves it), the one nearest the big-face crossing
-      if (!(a >= bmin && a <= bmax) || !(tn < 0.0)) return;
-      const double dd = fabs(a - astar);
-      if (dd < mbd) { mbd = dd; msa = a; mse = ms; msf = mf; }
-      return;
-    }
-    if (!(a > amin && a <= L)) return;
-    if (!(tn > 0.0)) return;
-    if (a < best) { best = a; bf = f; bu = uu; bv = vv; }
-  };
-  int mode = DONE;
-  bool drained = false;   // wave-uniform: the queue has no segment left
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ int face_root(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
+                                         const double* xs, const double* t, double L, const double* n1,
+                                         const double* n2, bool local, double us, double vs, double dr, double* box,
+                                         double& u, double& v, double& al, double& tn, double& off, bool& sole,
+                                         double* path) {
+  constexpr double kOver = 1.0 + 1e-4;
+  double p[3], pu[3], pv[3], prev = 1e300;
+  bool last = false;
 #pragma unroll 1
   while (true) {
-    if (!drained) {
-      const unsigned long long idle = __ballot(mode == DONE);
-      if (idle && (__popcll(idle) >= kRefill || __popcll(idle) == 64)) {
-        const int nidle = __popcll(idle);
-        const int leader = __ffsll((long long)idle) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(head, nidle);
-        base = __shfl(base, leader, 64);
-        if ((int64_t)base + nidle >= nq) drained = true;
-        if (mode == DONE) {
-          const int64_t i = (int64_t)base + lane_rank64(idle);
-          if (i < nq) {
-            p = trk_p[i];
-            xs[0] = trk_x[i]; xs[1] = trk_x[cap + i]; xs[2] = trk_x[2 * cap + i];
+    face_eval<NG>(cp, u, v, p, pu, pv);
+    const double r[3] = {p[0] - xs[0], p[1] - xs[1], p[2] - xs[2]};
+    const double bu = fabs(u - box[0]) + box[2] * kOver, bv = fabs(v - box[1]) + box[3] * kOver;
+    const double all = sqrt(bu * bu + bv * bv);
+    double reach = all;
+    if (local) reach = fmin(reach, sqrt((u - us) * (u - us) + (v - vs) * (v - vs)) + dr);
+    FaceRange R;
+    const bool some = face_range(X, r, t, L, pu, pv, reach, R);
+    double nrm[3];
+    cross3(pu, pv, nrm);
+    const double P0 = dot3(r, n1), P1 = dot3(r, n2);
+    al = dot3(r, t);
+    tn = dot3(nrm, t);
+    off = P0 * P0 + P1 * P1;
+    const double u0 = u - box[0], v0 = v - box[1];
+    if (!last) {
+      // no face point on the segment: it lies on one side of the tangent plane
+      // beyond the face's departure c2 rho^2 / 2 from it, or its image lies
+      // beyond an edge
+      if (!some) return ROOT_NONE;
+      const double il = 1.0 / sqrt(dot3(nrm, nrm)), h = 0.505 * (double)X.c2 * R.rho * R.rho + 1e-9 * F.diam;
+      const double d = -dot3(r, nrm) * il, d0 = d + R.lo * tn * il, d1 = d + R.hi * tn * il;
+      if (fmin(d0, d1) > h || fmax(d0, d1) < -h) return ROOT_NONE;
+      const double eu = box[2] + 1e-9 + R.h, ev = box[3] + 1e-9 + R.h;
+      if (fmin(u0 + R.ws[0], u0 + R.we[0]) > eu || fmax(u0 + R.ws[0], u0 + R.we[0]) < -eu ||
+          fmin(v0 + R.ws[1], v0 + R.we[1]) > ev || fmax(v0 + R.ws[1], v0 + R.we[1]) < -ev)
+        return ROOT_NONE;
+    }
+    const double a = dot3(pu, n1), b = dot3(pv, n1), c = dot3(pu, n2), d = dot3(pv, n2);
+    const double det = a * d - b * c;
+    const bool regular = fabs(det) > 0.0 && isfinite(det);
+    const double id = 1.0 / det;
+    const double A[4] = {d * id, -b * id, -c * id, a * id};
+    const double su = -(A[0] * P0 + A[1] * P1), sv = -(A[2] * P0 + A[3] * P1);
+    const double gu = box[2] * kOver, gv = box[3] * kOver;
+    const bool out = fabs(u0 + su) > gu || fabs(v0 + sv) > gv;
+    const double kap = root_contraction(F, X, n1, n2, A, R.rho);
+    if (regular && kap < kMaxContraction) {
+      if (last) {
+        if (local) {
+          // a root past the first exit, out of the reach bound's range?
+          face_range(X, r, t, L, pu, pv, all, R);
+          if (!(root_contraction(F, X, n1, n2, A, R.rho) < kMaxContraction)) sole = false;
+        }
+        return ROOT_ONE;
+      }
+      // a root on the segment would lie within kap / (1 - kap) of the step's end
+      const double rad = kap / (1.0 - kap) * sqrt(su * su + sv * sv) + 1e-9;
+      if (fabs(u0 + su) > rad + box[2] || fabs(v0 + sv) > rad + box[3]) return ROOT_NONE;
+    }
+    // a step that leaves the part or does not halve the one before, or a root
+    // that need not be the only one: halving the part settles it in fewer
+    // evaluations than more steps (passage faces, paths of 4 % of an element:
+    // 3.3 a face, 5.3 with two more such steps)
+    const double step = fabs(su) + fabs(sv);
+    if (!regular || last || out || !(step <= 0.5 * prev)) {
+      if (R.h < 4.0) {
+        const double l0 = fmax(-box[2], fmin(u0 + R.ws[0], u0 + R.we[0]) - R.h);
+        const double l1 = fmin(box[2], fmax(u0 + R.ws[0], u0 + R.we[0]) + R.h);
+        const double m0 = fmax(-box[3], fmin(v0 + R.ws[1], v0 + R.we[1]) - R.h);
+        const double m1 = fmin(box[3], fmax(v0 + R.ws[1], v0 + R.we[1]) + R.h);
+        box[0] += 0.5 * (l0 + l1);
+        box[2] = fmax(0.0, 0.5 * (l1 - l0));
+        box[1] += 0.5 * (m0 + m1);
+        box[3] = fmax(0.0, 0.5 * (m1 - m0));
+      }
+      const double iw = R.hi > R.lo ? 1.0 / (R.hi - R.lo) : 0.0;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              xe[k] = P.x[k * cap + p];
-              v[k] = P.v[k * cap + p];
-              kx[k] = P.kx[k * cap + p];
-              kv[k] = P.kv[k * cap + p];
-            }
-            e = e0 = P.elem[p];
-            hits = nseg = 0;
-            status = ACTIVE;
-            reach = trk_m[i];
-            excl = entry = -1;
-            count = 0;
-            mort = -1;
-            mode = NEW_LEG;
-          }
+      for (int k = 0; k < 2; ++k) {
+        path[2 + k] = (R.we[k] - R.ws[k]) * iw;
+        path[k] = (k ? v : u) + R.ws[k] - R.lo * path[2 + k];
+      }
+      if (regular && last) {
+        // the contraction bound is proportional to the radius
+        const double near = 0.7 * kMaxContraction * R.rho / kap;
+        if (near > 1e-5) {
+          off = near;
+          return ROOT_NEAR;
         }
       }
+      return ROOT_OPEN;
     }
-    if (__ballot(mode != DONE) == 0ull) break;
-    if (mode == NEW_LEG) {
-      t[0] = xe[0] - xs[0]; t[1] = xe[1] - xs[1]; t[2] = xe[2] - xs[2];
-      L = sqrt(dot3(t, t));
-      if (L == 0.0) {
-        mode = DONE;
-      } else {
-        double iL = 1.0 / L;
-        t[0] *= iL; t[1] *= iL; t[2] *= iL;
-        ray_planes(t, n1, n2);
-        eps = 1e-12 * m.hE[e];
-        best = 1e300;
-        bf = -1;
-        f = 0;
-        mode = NEXT_FACE;
-      }
-    }
-    if (mode == NEXT_FACE) {
-      // reach: the faces the first leg can reach (all of them on later legs)
-      while (f < 6 && (f == excl || !((reach >> f) & 1u) || !bbox_hit(m.faces[e * 6 + f], xs, xe))) f++;
-      if (f == 6) {
-        mode = LEG_END;
-      } else {
-        const FaceRec& F = m.faces[e * 6 + f];
-        fl = f;
-        amin = (f == entry) ? fmax(eps, kEntryRel * F.diam) : eps;
-        if (F.type != FACE_CURVED) {
-          double al[2], uv[4];
-          int nr = (F.type == FACE_PLANAR) ? planar_hit(F, xs, t, al, uv) : bilinear_hit(F, xs, t, al, uv);
-          for (int r = 0; r < nr; ++r) {
-            double pu[3], pv[3], nrm[3];
-            for (int k = 0; k < 3; ++k) {
-              pu[k] = F.A[k] * uv[2 * r + 1] + F.B[k];
-              pv[k] = F.A[k] * uv[2 * r] + F.C[k];
-            }
-            cross3(pu, pv, nrm);
-            consider(al[r], uv[2 * r], uv[2 * r + 1], kFaceSign[f] * dot3(nrm, t));
-          }
-          f++;
-        } else {
-          // only roots with displacement in (amin, L] matter: clip to a padded band
-          const double pad = 1e-9 * F.diam;
-          bmin = amin - pad;
-          bmax = L + pad;
-          cpf = m.cp + (size_t)(e * 6 + f) * (NG * NG * 3);
-          stk[0][0] = 0.0; stk[0][1] = 1.0; stk[0][2] = 0.0; stk[0][3] = 1.0;
-          sp = 1;
-          budget = kClipSteps;
-          mode = POP;
-        }
-      }
-    }
-    if (MORT && mode == MORT_FACE) {
-      // the small faces of the big mortar face just crossed (Sec. 3.2.3)
-      while (mj < 4 && (m.mortar[mort * 8 + 2 * mj] < 0 ||
-                        !bbox_hit(m.faces[m.mortar[mort * 8 + 2 * mj] * 6 + m.mortar[mort * 8 + 2 * mj + 1]], xs, xe)))
-        mj++;
-      if (mj == 4) {
-        mode = MORT_END;
-      } else {
-        ms = m.mortar[mort * 8 + 2 * mj];
-        mf = m.mortar[mort * 8 + 2 * mj + 1];
-        fl = mf;
-        const FaceRec& F = m.faces[ms * 6 + mf];
-        const double pad = 1e-9 * F.diam;
-        bmin = -pad;
-        bmax = L + pad;
-        if (F.type != FACE_CURVED) {
-          double al[2], uv[4];
-          int nr = (F.type == FACE_PLANAR) ? planar_hit(F, xs, t, al, uv) : bilinear_hit(F, xs, t, al, uv);
-          for (int r = 0; r < nr; ++r) {
-            double pu[3], pv[3], nrm[3];
-            for (int k = 0; k < 3; ++k) {
-              pu[k] = F.A[k] * uv[2 * r + 1] + F.B[k];
-              pv[k] = F.A[k] * uv[2 * r] + F.C[k];
-            }
-            cross3(pu, pv, nrm);
-            consider(al[r], uv[2 * r], uv[2 * r + 1], kFaceSign[mf] * dot3(nrm, t));
-          }
-          mj++;
-        } else {
-          cpf = m.cp + (size_t)(ms * 6 + mf) * (NG * NG * 3);
-          stk[0][0] = 0.0; stk[0][1] = 1.0; stk[0][2] = 0.0; stk[0][3] = 1.0;
-          sp = 1;
-          budget = kClipSteps;
-          mode = POP;
-        }
-      }
-    }
-    if (mode == POP) {
-      if (sp == 0 || budget <= 0) {
-        if (MORT && mort >= 0) {
-          mj++;
-          mode = MORT_FACE;
-        } else {
-          f++;
-          mode = NEXT_FACE;
-        }
-      } else {
-        --sp;
-        u0 = stk[sp][0]; u1 = stk[sp][1]; v0 = stk[sp][2]; v1 = stk[sp][3];
-        project_face<NG>(cpf, xs, t, n1, n2, q);
-        if (u0 != 0.0 || u1 != 1.0) patch_restrict<NG, 3>(q, 0, u0, u1);
-        if (v0 != 0.0 || v1 != 1.0) patch_restrict<NG, 3>(q, 1, v0, v1);
-        mode = CLIP;
-      }
-    }
-    if (mode == CLIP) {
-      // one Bezier-clipping iteration (Sec. 3.2.4) on the live box
-      double a, b;
-      mode = POP;
-      if (--budget >= 0 && !outside_band<NG>(q, bmin, bmax) && clip_dir<NG>(q, 0, bmin, bmax, a, b)) {
-        patch_restrict<NG, 3>(q, 0, a, b);
-        double w = u1 - u0;
-        double nu0 = u0 + a * w, nu1 = u0 + b * w;
-        u0 = nu0; u1 = nu1;
-        const double ru = b - a;
-        if (clip_dir<NG>(q, 1, bmin, bmax, a, b)) {
-          patch_restrict<NG, 3>(q, 1, a, b);
-          w = v1 - v0;
-          double nv0 = v0 + a * w, nv1 = v0 + b * w;
-          v0 = nv0; v1 = nv1;
-          const double rv = b - a;
-          const double wu = u1 - u0, wv = v1 - v0;
-          bool conv = (wu <= kBoxTol && wv <= kBoxTol) ||
-                      (wu <= kNewtonBox && wv <= kNewtonBox && ru <= kQuadRatio && rv <= kQuadRatio);
-          const bool su = (ru > 0.8 && wu > kBoxTol), sv = (rv > 0.8 && wv > kBoxTol);
-          if (!conv && (su || sv) && sp + 2 > kClipStack) conv = true;
-          if (conv) {
-            // 2-D Newton on the plane distances from the box centre
-            double u = (u0 + u1) - 1.0, vv = (v0 + v1) - 1.0;
-            double pp[3], pu[3], pv[3];
+    prev = step;
+    // a step this small leaves an error of its square: one more evaluation
+    last = step <= 1e-9;
+    u += su;
+    v += sv;
+  }
+}
+
+// The intersections of the segment with a part of a curved face that face_root
+// left open (near-tangential paths, long paths over strongly curved faces),
+// passed to root(al, u, v, t . (pu x pv)): the part is cut, carved around the
+// roots found and halved, down to kPartSize, where the last iterate is taken if
+// it lies on the line to 1e-9 face diameters, and for at most kMaxParts parts.
+constexpr int kPartStack = 32, kMaxParts = 256;
+constexpr double kPartSize = 1e-4;
+
+template <int NG, class Root>
+__device__ __forceinline__ void part_roots(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
+                                           const double* xs, const double* t, double L, const double* n1,
+                                           const double* n2, bool local, double us, double vs, double dr, double* box,
+                                           double u, double v, Root&& root) {
+  float stk[kPartStack][4];
+  int sp = 0, parts = 0;
+  bool sole = true;
+  // [a0, a1] x [b0, b1] to the stack, rounded outwards: the parts stay a cover
+  auto push = [&](double a0, double a1, double b0, double b1) {
+    if (!(a1 > a0) || !(b1 > b0) || sp >= kPartStack) return;
+    stk[sp][0] = (float)(0.5 * (a0 + a1));
+    stk[sp][1] = (float)(0.5 * (b0 + b1));
+    stk[sp][2] = (float)(0.5 * (a1 - a0)) * (1.0f + 1e-6f) + 1e-7f;
+    stk[sp][3] = (float)(0.5 * (b1 - b0)) * (1.0f + 1e-6f) + 1e-7f;
+    ++sp;
+  };
 #pragma unroll 1
-            for (int it = 0; it < 3; ++it) {
-              bezier_eval<NG>(cpf, u, vv, pp, pu, pv);
-              double r[3] = {pp[0] - xs[0], pp[1] - xs[1], pp[2] - xs[2]};
-              double G0 = dot3(r, n1), G1 = dot3(r, n2);
-              double Gu0 = dot3(pu, n1), Gu1 = dot3(pu, n2), Gv0 = dot3(pv, n1), Gv1 = dot3(pv, n2);
-              double det = Gu0 * Gv1 - Gu1 * Gv0;
-              if (det == 0.0 || !isfinite(det)) break;
-              u += -(G0 * Gv1 - G1 * Gv0) / det;
-              vv += -(Gu0 * G1 - Gu1 * G0) / det;
-            }
-            bezier_eval<NG>(cpf, u, vv, pp, pu, pv);
-            double r3[3] = {pp[0] - xs[0], pp[1] - xs[1], pp[2] - xs[2]}, nrm[3];
-            cross3(pu, pv, nrm);
-            consider(dot3(r3, t), u, vv, kFaceSign[fl] * dot3(nrm, t));
-          } else if (su || sv) {
-            const int dir = (su && sv) ? (wu >= wv ? 0 : 1) : (su ? 0 : 1);
-            if (dir == 0) {
-              const double um = 0.5 * (u0 + u1);
-              stk[sp][0] = um; stk[sp][1] = u1; stk[sp][2] = v0; stk[sp][3] = v1; sp++;
-              stk[sp][0] = u0; stk[sp][1] = um; stk[sp][2] = v0; stk[sp][3] = v1; sp++;
-            } else {
-              const double vm = 0.5 * (v0 + v1);
-              stk[sp][0] = u0; stk[sp][1] = u1; stk[sp][2] = vm; stk[sp][3] = v1; sp++;
-              stk[sp][0] = u0; stk[sp][1] = u1; stk[sp][2] = v0; stk[sp][3] = vm; sp++;
-            }
-          } else {
-            mode = CLIP;   // the box shrank: clip it again
-          }
+  while (true) {
+    double al, tn, off, path[4];
+    const double was = box[2] * box[3];
+    const int res = face_root<NG>(cp, F, X, xs, t, L, n1, n2, local, us, vs, dr, box, u, v, al, tn, off, sole, path);
+    ++parts;
+    if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, v, tn);
+    if (res >= ROOT_NEAR) {
+      const double l0 = box[0] - box[2], l1 = box[0] + box[2], m0 = box[1] - box[3], m1 = box[1] + box[3];
+      if (parts >= kMaxParts) break;
+      if (res == ROOT_NEAR) {
+        // the box without the square around the root
+        const double a0 = fmax(l0, u - off), a1 = fmin(l1, u + off);
+        push(l0, a0, m0, m1);
+        push(a1, l1, m0, m1);
+        push(a0, a1, m0, fmax(m0, v - off));
+        push(a0, a1, fmin(m1, v + off), m1);
+      } else if (fmax(box[2], box[3]) < kPartSize) {
+        if (off <= 1e-18 * F.diam * F.diam) root(al, u, v, tn);
+      } else {
+        // the open part again if the cut took half of it, else its two halves
+        if (box[2] * box[3] < 0.5 * was) {
+          u = box[0];
+          v = box[1];
+          continue;
+        }
+        if (box[2] >= box[3]) {
+          push(l0, box[0], m0, m1);
+          push(box[0], l1, m0, m1);
+        } else {
+          push(l0, l1, m0, box[1]);
+          push(l0, l1, box[1], m1);
         }
       }
     }
-    if (mode == LEG_END) {
-      if (bf < 0) {
-        mode = DONE;
-      } else if (count >= max_cross) {
-        status = MAX_CROSS;
-        mode = DONE;
-      } else {
-        count++;
-        nseg++;
-        double xh[3] = {xs[0] + best * t[0], xs[1] + best * t[1], xs[2] + best * t[2]};
-        const int fid = e * 6 + bf;
-        const FaceRec& F = m.faces[fid];
-        const int bc = F.bc;
-        mode = NEW_LEG;
-        reach = 0x3Fu;
-        if (bc == BC_INTERNAL || bc == BC_PERIODIC) {
-          const int ne = F.nbr_elem, nf = F.nbr_face;
-          if (bc == BC_PERIODIC)
-            for (int k = 0; k < 3; ++k) { xh[k] += F.shift[k]; xe[k] += F.shift[k]; }
-          e = ne;
-          const bool planar = m.faces[ne * 6 + nf].type == FACE_PLANAR;
-          excl = planar ? nf : -1;
-          entry = planar ? -1 : nf;
-          xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
-        } else if (MORT && bc == BC_MORTAR) {
-          // non-conforming side: find the small face the path enters through
-          mort = F.nbr_elem;
+    if (sp == 0) break;
+    --sp;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) box[k] = (double)stk[sp][k];
+    u = box[0];
+    v = box[1];
+  }
+}
+
+// displacements [a0, a1] of the segment's piece that a lane searches: 39 equal
+// pieces of 1/40, then halving towards the start, where the last crossing left
+// a root that a nearly tangential path may have its next one close to
+__device__ __forceinline__ void segment_piece(int lane, double L, double& a0, double& a1) {
+  const double w = L * 0.025;
+  if (lane < 39) {
+    a1 = L - w * lane;
+    a0 = a1 - w;
+  } else {
+    a1 = ldexp(w, 39 - lane);
+    a0 = lane < 63 ? 0.5 * a1 : 0.0;
+  }
+}
+
+// in-face coordinates (the two free axes in increasing order) of xi on face f
+__device__ __forceinline__ void face_coords(int f, const double* xi, double& u, double& v) {
+  u = f < 2 ? xi[1] : xi[0];
+  v = f < 4 ? xi[2] : xi[1];
+}
+
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const unsigned long long b = __double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Physical-space tracking (Sec. 3.2.3) of the queued straight stage segments
+// q_x -> P.x[p], 64 at a time per wavefront: smallest alpha in
+// (1e-12 h_e, remaining length] with (u, v) in [-1,1]^2, ties to the lowest
+// local face; hand-off, periodic shift, specular reflection (Sec. 2.4) of the
+// remaining displacement, v and the stage registers; open boundaries end the
+// particle.  q_s: reference coordinates of the segment start; q_m: the faces
+// the first leg can reach.
+//
+// Every iteration takes each lane one face further (or to its next leg).  A
+// curved face is one Newton search per lane (face_root); a face that leaves
+// open is searched by the whole wavefront, 64 parts of it at once, which reads
+// that face's data through uniform addresses.  Bezier clipping, which this
+// replaces, held the projected patch (75 doubles for degree 4, 147 for degree
+// 6, spilled) at one wavefront per SIMD and took some 30 long iterations for
+// the slowest lane of a wavefront; a Newton search takes 1 (no crossing) to 4
+// evaluations of the face and needs no patch.  Measured per stage: 1.6e5
+// segments of degree 4 (1e6 particles, 32^3 box) 431 -> 148 us, 3e5 of degree
+// 6 (1e6 particles, annular passage) 3003 -> 1383 us, 1300 segments (4^3 box)
+// 116 -> 32 us.  What is left is the FP64 issue of the bounds (about as long as
+// the evaluation itself) and, on the passage, the wavefronts with the most
+// open faces.
+//
+// A root counts if it lies on the face and the path leaves the element there
+// (t . outward normal > 0; at a tangential touch or the entry point the path
+// enters).  excl: face just met whose only root that is; entry: non-planar
+// face just met whose root at that point (alpha ~ 0, error growing like
+// 1/sin(incidence)) is ignored below kEntryRel * face diameter.
+template <int NG, bool MORT>
+__device__ void track_queue(const MeshView& m, const Particles& P, const int32_t* __restrict__ q_p,
+                            const double* __restrict__ q_x, const float* __restrict__ q_s,
+                            const uint8_t* __restrict__ q_m, int64_t nq, int max_cross, int& ncross, int& nhits) {
+  const int64_t cap = P.cap;
+  const int lane = threadIdx.x & 63;
+  for (int64_t base = (int64_t)blockIdx.x * 64; base < nq; base += (int64_t)gridDim.x * 64) {
+    const int64_t i = base + lane;
+    const bool have = i < nq;
+    const int64_t p = have ? q_p[i] : 0;
+    enum { DONE, NEW_LEG, FACES };
+    int mode = have ? NEW_LEG : DONE;
+    double xs[3] = {0, 0, 0}, xe[3] = {0, 0, 0}, v[3] = {0, 0, 0}, kx[3] = {0, 0, 0}, kv[3] = {0, 0, 0};
+    double xi[3] = {0, 0, 0}, t[3] = {0, 0, 0}, L = 0.0, best = 1e300, bu = 0.0, bv = 0.0;
+    unsigned reach = 0, todo = 0;
+    int e0 = 0, e = 0, hits = 0, nseg = 0, excl = -1, entry = -1, bf = -1;
+    int8_t status = ACTIVE;
+    bool known = true;    // xi: the leg start's reference coordinates
+    bool sole = false;    // the best face has no other root on the segment
+    // mort: the small faces of a big mortar face just crossed (Sec. 3.2.3) are
+    // searched for the root nearest that crossing where the path enters the
+    // small element
+    int mort = -1, mj = 0, mse = -1, msf = -1;
+    double mbd = 1e300, msa = 0.0;
+    if (have) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        xs[k] = q_x[k * cap + i];
+        xi[k] = (double)q_s[k * cap + i];
+        xe[k] = P.x[k * cap + p];
+      }
+      e0 = e = P.elem[p];
+      reach = q_m[i];
+    }
+#pragma unroll 1
+    while (__ballot(mode != DONE) != 0ull) {
+      if (mode == NEW_LEG) {
+        t[0] = xe[0] - xs[0]; t[1] = xe[1] - xs[1]; t[2] = xe[2] - xs[2];
+        L = sqrt(dot3(t, t));
+        if (L == 0.0) {
+          mode = DONE;
+        } else {
+          const double iL = 1.0 / L;
+          t[0] *= iL; t[1] *= iL; t[2] *= iL;
+          best = 1e300;
+          bf = -1;
+          sole = false;
+          mort = -1;
           mj = 0;
           mse = -1;
           mbd = 1e300;
-          astar = best;
-          mbig = bf;
-          mode = MORT_FACE;
-        } else if (bc == BC_REFLECT) {
-          double nrm[3];
-          if (F.type == FACE_CURVED) {
-            double pp[3], pu[3], pv[3];
-            bezier_eval<NG>(m.cp + (size_t)fid * (NG * NG * 3), bu, bv, pp, pu, pv);
-            cross3(pu, pv, nrm);
-          } else {
-            double pu[3], pv[3];
-            for (int k = 0; k < 3; ++k) { pu[k] = F.A[k] * bv + F.B[k]; pv[k] = F.A[k] * bu + F.C[k]; }
-            cross3(pu, pv, nrm);
+          todo = 0;
+          mode = FACES;
+#pragma unroll 1
+          for (int f = 0; f < 6; ++f)
+            if (f != excl && ((reach >> f) & 1u) && bbox_hit(m.faces[(size_t)e * 6 + f], xs, xe)) todo |= 1u << f;
+        }
+      }
+      // the lane's next face: element ef, local face f
+      int ef = -1, f = 0;
+      if (mode == FACES) {
+        if (MORT && !todo && mort < 0 && bf >= 0 && nseg < max_cross && m.faces[(size_t)e * 6 + bf].bc == BC_MORTAR)
+          mort = m.faces[(size_t)e * 6 + bf].nbr_elem;
+        if (MORT && mort >= 0) {
+          while (mj < 4 && ef < 0) {
+            const int se = m.mortar[mort * 8 + 2 * mj], sf = m.mortar[mort * 8 + 2 * mj + 1];
+            mj++;
+            if (se >= 0 && bbox_hit(m.faces[(size_t)se * 6 + sf], xs, xe)) {
+              ef = se;
+              f = sf;
+            }
           }
-          const double il = 1.0 / sqrt(dot3(nrm, nrm));
-          nrm[0] *= il; nrm[1] *= il; nrm[2] *= il;
-          const double r[3] = {xe[0] - xh[0], xe[1] - xh[1], xe[2] - xh[2]};
-          const double dr = dot3(r, nrm), dv = dot3(v, nrm), dkx = dot3(kx, nrm), dkv = dot3(kv, nrm);
+        } else if (todo) {
+          ef = e;
+          f = __builtin_ctz(todo);
+          todo &= todo - 1u;
+        }
+      }
+      const bool test = ef >= 0;
+      const bool small = MORT && mort >= 0;
+      // a root of the face under test against what the leg has so far
+      auto take = [&](double al, double ru, double rv, bool alone) {
+        if (small) {
+          const double dd = fabs(al - best);
+          if (dd < mbd) { mbd = dd; msa = al; mse = ef; msf = f; }
+        } else if (al < best) {
+          best = al; bf = f; bu = ru; bv = rv; sole = alone;
+        }
+      };
+      const FaceRec& F = m.faces[test ? (size_t)ef * 6 + f : 0];
+      double amin = 0.0, amax = 0.0, sign = 1.0;   // roots in (amin, amax] with sign * t . (pu x pv) > 0
+      if (test) {
+        const double eps = 1e-12 * m.hE[e], pad = 1e-9 * F.diam;
+        amin = small ? -pad : (f == entry) ? fmax(eps, kEntryRel * F.diam) : eps;
+        amax = small ? L + pad : L;
+        sign = small ? -kFaceSign[f] : kFaceSign[f];
+      }
+      bool curved = false;
+      if (test && (NG == 2 || F.type != FACE_CURVED)) {
+        double al[2], uv[4];
+        const int nr = (F.type == FACE_PLANAR) ? planar_hit(F, xs, t, al, uv) : bilinear_hit(F, xs, t, al, uv);
+        for (int r = 0; r < nr; ++r) {
+          double pu[3], pv[3], nrm[3];
           for (int k = 0; k < 3; ++k) {
-            xe[k] = xh[k] + (r[k] - 2.0 * dr * nrm[k]);
-            v[k] -= 2.0 * dv * nrm[k];
-            kx[k] -= 2.0 * dkx * nrm[k];
-            kv[k] -= 2.0 * dkv * nrm[k];
+            pu[k] = F.A[k] * uv[2 * r + 1] + F.B[k];
+            pv[k] = F.A[k] * uv[2 * r] + F.C[k];
           }
-          hits++;
-          excl = (F.type == FACE_PLANAR) ? bf : -1;
-          entry = (F.type == FACE_PLANAR) ? -1 : bf;
-          xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
-        } else {
-          status = OPEN_EXIT;
-          xe[0] = xh[0]; xe[1] = xh[1]; xe[2] = xh[2];
+          cross3(pu, pv, nrm);
+          if (fabs(uv[2 * r]) <= 1.0 + kUVEps && fabs(uv[2 * r + 1]) <= 1.0 + kUVEps && al[r] > amin && al[r] <= amax &&
+              sign * dot3(nrm, t) > 0.0)
+            take(al[r], uv[2 * r], uv[2 * r + 1], false);
+        }
+      } else {
+        curved = test;
+      }
+      if constexpr (NG > 2) {
+        double us = 0.0, vs = 0.0, dr = 0.0, n1[3], n2[3], box[4] = {0.0, 0.0, 1.0, 1.0}, path[4];
+        bool local = false, open = false;
+        if (curved) {
+          if (known && !small) {
+            face_coords(f, xi, us, vs);
+            us = fmin(1.0, fmax(-1.0, us));
+            vs = fmin(1.0, fmax(-1.0, vs));
+            // the crossing of an internal face lies where the path can get to
+            // inside the element (the sampled bound; a crossing it misses is
+            // repaired by the location step)
+            if (F.bc == BC_INTERNAL) {
+              double g0, g1;
+              face_coords(f, m.gxi + (size_t)e * 6, g0, g1);
+              dr = L * sqrt(g0 * g0 + g1 * g1) + 1e-6;
+              local = true;
+            }
+          }
+          ray_planes(t, n1, n2);
+          double u = us, w = vs, al, tn, off;
+          bool alone = true;
+          const size_t id = (size_t)ef * 6 + f;
+          const int res = face_root<NG>(m.cp + id * (NG * NG * 3), F, m.fext[id], xs, t, L, n1, n2, local, us, vs, dr,
+                                        box, u, w, al, tn, off, alone, path);
+          open = res >= ROOT_NEAR;
+          if ((res == ROOT_ONE || res == ROOT_NEAR) && fabs(u) <= 1.0 + kUVEps && fabs(w) <= 1.0 + kUVEps &&
+              al > amin && al <= amax && sign * tn > 0.0)
+            take(al, u, w, alone && !open);
+        }
+        // open faces, one after the other, by the whole wavefront: first each lane
+        // takes one of 8 x 8 parts of the open part; a part that this leaves open
+        // (one in four faces has one: a nearly tangential path) is searched again
+        // with each lane on one piece of the segment, from the piece's image
+        unsigned long long left = __ballot(open);
+#pragma unroll 1
+        while (left) {
+          const int src = __ffsll((long long)left) - 1;
+          left &= left - 1ull;
+          const int gid = __builtin_amdgcn_readlane(ef * 6 + f, src);
+          const FaceRec& Fo = m.faces[(size_t)gid];
+          const FaceExt& Xo = m.fext[(size_t)gid];
+          const double* co = m.cp + (size_t)gid * (NG * NG * 3);
+          double oxs[3], ot[3], o1[3], o2[3], cell[4], cpath[4];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            oxs[k] = lane_value(xs[k], src);
+            ot[k] = lane_value(t[k], src);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) cell[k] = lane_value(box[k], src);
+          const double oL = lane_value(L, src), ous = lane_value(us, src), ovs = lane_value(vs, src);
+          const double odr = lane_value(dr, src), omin = lane_value(amin, src), omax = lane_value(amax, src);
+          const double osign = lane_value(sign, src), oref = lane_value(small ? best : 0.0, src);
+          const bool olocal = __builtin_amdgcn_readlane((int)local, src) != 0;
+          const bool osmall = MORT && __builtin_amdgcn_readlane((int)small, src) != 0;
+          ray_planes(ot, o1, o2);
+          double key = 1e300, ka = 0.0, ku = 0.0, kw = 0.0;
+          auto root = [&](double al, double ru, double rw, double tn) {
+            if (fabs(ru) > 1.0 + kUVEps || fabs(rw) > 1.0 + kUVEps || !(al > omin && al <= omax) || !(osign * tn > 0.0))
+              return;
+            const double d = osmall ? fabs(al - oref) : al;
+            if (d < key) { key = d; ka = al; ku = ru; kw = rw; }
+          };
+          cell[0] += cell[2] * (0.25 * (lane & 7) - 0.875);
+          cell[1] += cell[3] * (0.25 * (lane >> 3) - 0.875);
+          cell[2] *= 0.125;
+          cell[3] *= 0.125;
+          unsigned long long again;
+          {
+            double u = cell[0], w = cell[1], al, tn, off;
+            bool alone = true;
+            const int res = face_root<NG>(co, Fo, Xo, oxs, ot, oL, o1, o2, olocal, ous, ovs, odr, cell, u, w, al, tn,
+                                          off, alone, cpath);
+            if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, w, tn);
+            again = __ballot(res >= ROOT_NEAR);
+          }
+#pragma unroll 1
+          while (again) {
+            const int c = __ffsll((long long)again) - 1;
+            again &= again - 1ull;
+            double b[4], a0, a1, ps[3];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[k] = lane_value(cell[k], c);
+            segment_piece(lane, oL, a0, a1);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ps[k] = oxs[k] + a0 * ot[k];
+            const double am = 0.5 * (a0 + a1);
+            const double u = lane_value(cpath[0], c) + am * lane_value(cpath[2], c);
+            const double w = lane_value(cpath[1], c) + am * lane_value(cpath[3], c);
+            part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, olocal, ous, ovs, odr, b,
+                           fmin(b[0] + b[2], fmax(b[0] - b[2], u)), fmin(b[1] + b[3], fmax(b[1] - b[3], w)),
+                           [&](double al, double ru, double rw, double tn) { root(a0 + al, ru, rw, tn); });
+          }
+          double low = key;
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) low = fmin(low, __shfl_xor(low, o, 64));
+          if (low < 1e300) {
+            const int at = __ffsll((long long)__ballot(key == low)) - 1;
+            const double al = lane_value(ka, at), ru = lane_value(ku, at), rw = lane_value(kw, at);
+            if (lane == src) {
+              take(al, ru, rw, false);
+              if (!small && bf == f) sole = false;
+            }
+          }
+        }
+      }
+      if (mode == FACES && !test) {
+        // end of the leg
+        if (bf < 0) {
           mode = DONE;
+        } else if (nseg >= max_cross) {
+          status = MAX_CROSS;
+          mode = DONE;
+        } else {
+          nseg++;
+          mode = NEW_LEG;
+          double xh[3] = {xs[0] + best * t[0], xs[1] + best * t[1], xs[2] + best * t[2]};
+          const FaceRec& B = m.faces[(size_t)e * 6 + bf];
+          const int bc = B.bc;
+          const bool bent = NG > 2 && B.type == FACE_CURVED;
+          excl = entry = -1;
+          reach = 0x3Fu;
+          known = false;
+          if (bc == BC_INTERNAL || bc == BC_PERIODIC) {
+            const int ne = B.nbr_elem, nf = B.nbr_face, orient = m.fext[(size_t)e * 6 + bf].orient;
+            const FaceRec& N = m.faces[(size_t)ne * 6 + nf];
+            if (bc == BC_PERIODIC)
+              for (int k = 0; k < 3; ++k) { xh[k] += B.shift[k]; xe[k] += B.shift[k]; }
+            // the same surface seen from the neighbour (a big mortar face
+            // reaches further than the small one): no other root there either
+            if (N.type == FACE_PLANAR || (sole && bent && N.type == FACE_CURVED && orient < 8)) excl = nf;
+            else entry = nf;
+            if (orient < 8) {
+              known = true;
+              const double s0 = (orient & 1) ? bv : bu, s1 = (orient & 1) ? bu : bv;
+              const double c0 = (orient & 2) ? -s0 : s0, c1 = (orient & 4) ? -s1 : s1;
+              const double side = (nf & 1) ? 1.0 : -1.0;
+              xi[0] = nf < 2 ? side : c0;
+              xi[1] = nf < 2 ? c0 : nf < 4 ? side : c1;
+              xi[2] = nf < 4 ? c1 : side;
+            }
+            e = ne;
+          } else if (MORT && bc == BC_MORTAR) {
+            if (mse >= 0) {
+              // continue from the small-face crossing in the small element
+              xh[0] = xs[0] + msa * t[0]; xh[1] = xs[1] + msa * t[1]; xh[2] = xs[2] + msa * t[2];
+              e = mse;
+              const bool planar = m.faces[(size_t)mse * 6 + msf].type == FACE_PLANAR;
+              excl = planar ? msf : -1;
+              entry = planar ? -1 : msf;
+            } else {
+              // no small face found (rounding at a seam): the leg ends in the big
+              // element and the next location step finds the particle
+              entry = bf;
+            }
+          } else if (bc == BC_REFLECT) {
+            double pp[3], pu[3], pv[3], nrm[3];
+            if (bent) {
+              face_eval<NG>(m.cp + ((size_t)e * 6 + bf) * (NG * NG * 3), bu, bv, pp, pu, pv);
+            } else {
+              for (int k = 0; k < 3; ++k) { pu[k] = B.A[k] * bv + B.B[k]; pv[k] = B.A[k] * bu + B.C[k]; }
+            }
+            cross3(pu, pv, nrm);
+            const double il = 1.0 / sqrt(dot3(nrm, nrm));
+            nrm[0] *= il; nrm[1] *= il; nrm[2] *= il;
+            if (hits == 0)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                v[k] = P.v[k * cap + p];
+                kx[k] = P.kx[k * cap + p];
+                kv[k] = P.kv[k * cap + p];
+              }
+            const double r[3] = {xe[0] - xh[0], xe[1] - xh[1], xe[2] - xh[2]};
+            const double dx = dot3(r, nrm), dv = dot3(v, nrm), dkx = dot3(kx, nrm), dkv = dot3(kv, nrm);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              xe[k] = xh[k] + (r[k] - 2.0 * dx * nrm[k]);
+              v[k] -= 2.0 * dv * nrm[k];
+              kx[k] -= 2.0 * dkx * nrm[k];
+              kv[k] -= 2.0 * dkv * nrm[k];
+            }
+            hits++;
+            known = true;
+            const double side = (bf & 1) ? 1.0 : -1.0;
+            xi[0] = bf < 2 ? side : bu;
+            xi[1] = bf < 2 ? bu : bf < 4 ? side : bv;
+            xi[2] = bf < 4 ? bv : side;
+            excl = (B.type == FACE_PLANAR) ? bf : -1;
+            entry = (B.type == FACE_PLANAR) ? -1 : bf;
+            if constexpr (NG > 2) {
+              if (bent) {
+                // the hit point is the reflected path's only point on this face
+                // if the contraction bound says so
+                double s[3] = {xe[0] - xh[0], xe[1] - xh[1], xe[2] - xh[2]}, m1[3], m2[3];
+                const double l2 = dot3(s, s);
+                if (l2 > 0.0) {
+                  const double l1 = sqrt(l2), i2 = 1.0 / l1, zero[3] = {0.0, 0.0, 0.0};
+                  s[0] *= i2; s[1] *= i2; s[2] *= i2;
+                  ray_planes(s, m1, m2);
+                  const double a = dot3(pu, m1), b = dot3(pv, m1), c = dot3(pu, m2), d = dot3(pv, m2);
+                  const double id = 1.0 / (a * d - b * c);
+                  const double A[4] = {d * id, -b * id, -c * id, a * id};
+                  const FaceExt& X = m.fext[(size_t)e * 6 + bf];
+                  FaceRange R;
+                  face_range(X, zero, s, l1, pu, pv, 2.83, R);
+                  if (root_contraction(B, X, m1, m2, A, R.rho) < kMaxContraction) {
+                    excl = bf;
+                    entry = -1;
+                  }
+                }
+              }
+            }
+          } else {
+            status = OPEN_EXIT;
+            xe[0] = xh[0]; xe[1] = xh[1]; xe[2] = xh[2];
+            mode = DONE;
+          }
+          xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
+          if (known) {
+            // as for the first leg: internal faces out of reach are dropped
+            const double d[3] = {xe[0] - xs[0], xe[1] - xs[1], xe[2] - xs[2]};
+            reach = reachable_faces(m, e, xi, dot3(d, d)) | boundary_faces(m.faces + (size_t)e * 6);
+          }
         }
       }
     }
-    if (MORT && mode == MORT_END) {
-      if (mse >= 0) {
-        // continue from the small-face crossing in the small element
-        e = mse;
-        const bool planar = m.faces[mse * 6 + msf].type == FACE_PLANAR;
-        excl = planar ? msf : -1;
-        entry = planar ? -1 : msf;
-        xs[0] += msa * t[0]; xs[1] += msa * t[1]; xs[2] += msa * t[2];
-      } else {
-        // no small face found (rounding at a seam): the leg ends in the big
-        // element and the next location step finds the particle
-        xs[0] += astar * t[0]; xs[1] += astar * t[1]; xs[2] += astar * t[2];
-        excl = -1;
-        entry = mbig;
-      }
-      mort = -1;
-      mode = NEW_LEG;
-      reach = 0x3Fu;
-    }
-    if (mode == DONE && p >= 0) {
-      // segment done: write back what changed
-      ncross += nseg;
-      nhits += hits;
-      if (nseg || status != ACTIVE) {
+    ncross += nseg;
+    nhits += hits;
+    if (nseg || status != ACTIVE) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) P.x[k * cap + p] = xe[k];
+      if (hits)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          P.x[k * cap + p] = xe[k];
           P.v[k * cap + p] = v[k];
           P.kx[k * cap + p] = kx[k];
           P.kv[k * cap + p] = kv[k];
         }
-        if (e != e0) P.elem[p] = e;
-        if (hits) P.hits[p] += hits;
-        if (status != ACTIVE) P.status[p] = status;
-        P.xi[p] = NAN;   // the continued reference coordinates no longer hold
-      }
-      p = -1;
+      if (e != e0) P.elem[p] = e;
+      if (hits) P.hits[p] += hits;
+      if (status != ACTIVE) P.status[p] = status;
+      P.xi[p] = NAN;   // the continued reference coordinates no longer hold
     }
   }
 }

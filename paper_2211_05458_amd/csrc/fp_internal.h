@@ -7,9 +7,6 @@
 namespace fp {
 
 constexpr int kMaxNodes = 8;        // n = N+1 <= 8, ng = Ngeo+1 <= 7
-constexpr int kClipStack = 16;      // Bezier-clipping interval stack
-constexpr int kClipSteps = 64;      // clipping iterations per face test
-constexpr int kMaxRoots = 8;
 constexpr int kMlpMaxBatch = 8192;   // rows per MLP gradient evaluation
 constexpr int kMlpStaticRows = 4096; // rows of fp_mlp_loss_grad_static (fixed device array)
 constexpr int kMlpIn = 84;           // learned-guess inputs: corners, curvature, point
@@ -23,8 +20,6 @@ constexpr double kNewtonTol = 1e-10;
 constexpr double kNewtonTolMixed = 1e-5;
 constexpr double kInsideEps = 1e-10;
 constexpr double kUVEps = 1e-12;
-constexpr double kClipTol = 1e-12;
-constexpr double kClipPad = 1e-10;
 constexpr double kEntryRel = 1e-9;   // entry-face root threshold, relative to the face diameter
 // sign that turns dp/du x dp/dv of local face f into its outward normal (face
 // parameters are the two other reference axes in increasing order, J > 0)
@@ -49,11 +44,26 @@ struct FaceRec {
   int32_t type, nbr_elem, nbr_face, bc;
 };
 
+// Bounds of one curved face for the tracker's root certificate (face_root),
+// all of them with a margin of 3 % (they are used slightly beyond the face).
+// With pu, pv the tangents of the face and w = (u, v):
+//   B (2x3, rows): |B pu - e1| and |B pv - e2| together stay below eps over
+//   the face, so |w - w'| <= |B (p - p')| inv1e, inv1e = 1 / (1 - eps) (0: eps too large);
+//   c2 bounds the norm of the second derivative of p, cn, c1, c2f its
+//   components along the slab frame nrm, e1, e2 of FaceRec.
+// orient: how the neighbour's face parameters follow from this face's (bit 0:
+// swapped, bit 1: first one reversed, bit 2: second one reversed; 8: unknown).
+struct FaceExt {
+  float B[6], inv1e, c2, cn, c1, c2f;
+  int32_t orient;
+};
+
 // Everything a kernel needs to know about the mesh (passed by value).
 struct MeshView {
   int32_t E, ng, n, n_geo;
   const double* X;        // [E][ng^3][3]
   const FaceRec* faces;   // [E*6]
+  const FaceExt* fext;    // [E*6]
   const double* cp;       // [E*6][ng*ng][3]
   const double* hE;       // [E]
   const double* xnode;    // [E][n^3][3] physical DG node positions

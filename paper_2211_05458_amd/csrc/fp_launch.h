@@ -8,8 +8,8 @@ namespace fp {
 bool supported(int n, int ng);
 
 hipError_t launch_face_setup(const MeshView& m, const double* X, const int32_t* nbr_elem, const int32_t* nbr_face,
-                             const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, double* cp,
-                             hipStream_t s);
+                             const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, FaceExt* fext,
+                             double* cp, hipStream_t s);
 hipError_t launch_nodes(const MeshView& m, double* xnode, double* vol, double* hE, double* nbox, double* gxi,
                         int32_t* bad, unsigned long long* node_pad, hipStream_t s);
 hipError_t launch_locate(const MeshView& m, const Particles& P, const int32_t* hint, int64_t n, hipStream_t s);
@@ -33,6 +33,7 @@ struct StageLaunch {
   int32_t* trk_p;           // [cap]
   double* trk_x;            // [3][cap]
   uint8_t* trk_m;           // [cap] faces the first leg can reach
+  float* trk_s;             // [3][cap] reference coordinates of the segment start
   unsigned long long* stats;
   hipEvent_t ev[8];         // optional (start, end) pairs around the elem, lane, track and learned-guess kernels
 };

@@ -15,7 +15,8 @@ struct MinvArg { double v[kMaxNodes * kMaxNodes]; };
 template <int NG>
 __global__ void k_face_setup(int E, const double* __restrict__ X, const int32_t* __restrict__ nbr_elem,
                              const int32_t* __restrict__ nbr_face, const int8_t* __restrict__ bc,
-                             const double* __restrict__ shift, MinvArg Mi, FaceRec* faces, double* cpo) {
+                             const double* __restrict__ shift, MinvArg Mi, FaceRec* faces, FaceExt* fext,
+                             double* cpo) {
   int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= E * 6) return;
   int e = gid / 6, f = gid % 6;
@@ -26,6 +27,10 @@ __global__ void k_face_setup(int E, const double* __restrict__ X, const int32_t*
   F.bc = bc[gid];
   for (int q = 0; q < 3; ++q) F.shift[q] = shift[gid * 3 + q];
   faces[gid] = F;
+  FaceExt B;
+  face_bounds<NG>(cpo + (size_t)gid * NG * NG * 3, F, B);
+  B.orient = (F.bc == BC_INTERNAL || F.bc == BC_PERIODIC) ? face_orientation<NG>(X, e, f, F) : 8;
+  fext[gid] = B;
 }
 
 // DG node positions x(xi_ijk), volumes w_i w_j w_k J(xi_ijk), element length scale
@@ -367,16 +372,16 @@ bool supported(int n, int ng) {
 static inline dim3 grid_for(int64_t n, int bs = 256) { return dim3((unsigned)((n + bs - 1) / bs)); }
 
 hipError_t launch_face_setup(const MeshView& m, const double* X, const int32_t* nbr_elem, const int32_t* nbr_face,
-                             const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, double* cp,
-                             hipStream_t s) {
+                             const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, FaceExt* fext,
+                             double* cp, hipStream_t s) {
   MinvArg Mi;
   for (int i = 0; i < kMaxNodes * kMaxNodes; ++i) Mi.v[i] = (i < m.ng * m.ng) ? Minv[i] : 0.0;
   dim3 g = grid_for((int64_t)m.E * 6, 128);
   switch (m.ng) {
-    case 2: k_face_setup<2><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, cp); break;
-    case 3: k_face_setup<3><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, cp); break;
-    case 5: k_face_setup<5><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, cp); break;
-    case 7: k_face_setup<7><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, cp); break;
+    case 2: k_face_setup<2><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
+    case 3: k_face_setup<3><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
+    case 5: k_face_setup<5><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
+    case 7: k_face_setup<7><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -159,23 +159,15 @@ __device__ __forceinline__ void interp_f32_mfma(const MeshView& m, const float* 
   }
 }
 
-// local faces of an element that are not internal (wall, open, periodic,
-// mortar): their crossings cannot be repaired by following xi to a neighbour
-__device__ __forceinline__ unsigned boundary_faces(const FaceRec* __restrict__ Fe) {
-  unsigned b = 0;
-#pragma unroll
-  for (int f = 0; f < 6; ++f) b |= (Fe[f].bc != BC_INTERNAL ? 1u : 0u) << f;
-  return b;
-}
-
 struct Task { int32_t e, p0, cnt, pad; };
 
 struct Queues {
-  int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word), [2] next tracking entry
+  int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word)
   int32_t* strag;     // [cap]
   int32_t* trk_p;     // [cap]
   double* trk_x;      // [3][cap] segment start
   uint8_t* trk_m;     // [cap] local faces the segment can reach (bit f)
+  float* trk_s;       // [3][cap] reference coordinates of the segment start
 };
 
 // Tasks of up to 64 particles: one per wavefront, four wavefronts per
@@ -358,6 +350,8 @@ void k_stage_elem(MeshView m, const double* __restrict__ X, const double* __rest
     q.trk_x[s2] = xs0;
     q.trk_x[cap + s2] = xs1;
     q.trk_x[2 * cap + s2] = xs2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q.trk_s[k * cap + s2] = (float)xi[k];
   }
   wave_add(stats + ST_NEWTON_IT * kStatSlots, it_sum);
   wave_add(stats + ST_NEWTON_CALLS * kStatSlots, calls);
@@ -386,6 +380,7 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
     bool trk = false;
     int64_t p = 0;
     double xs0 = 0, xs1 = 0, xs2 = 0;
+    float sx[3] = {0.f, 0.f, 0.f};
     unsigned reach = 0x3Fu;
     bool have = i < count;
     if (list) {
@@ -502,6 +497,8 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
             }
           }
           xs0 = x[0]; xs1 = x[1]; xs2 = x[2];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) sx[k] = (float)xi[k];
         }
       }
     }
@@ -512,6 +509,8 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
       q.trk_x[s] = xs0;
       q.trk_x[cap + s] = xs1;
       q.trk_x[2 * cap + s] = xs2;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) q.trk_s[k * cap + s] = sx[k];
     }
   }
   wave_add(stats + ST_NEWTON_IT * kStatSlots, it_sum);
@@ -522,18 +521,19 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
 }
 
 // MORT: the mesh has non-conforming (mortar) faces; conforming meshes run the
-// variant without that part of the state machine (fewer registers)
+// variant without that part (fewer registers)
 template <int NG, bool MORT>
-__global__ __launch_bounds__(256) void k_track(MeshView m, Particles P, Queues q, StepParams sp,
-                                               unsigned long long* stats) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_track(MeshView m, Particles P,
+                                                                                      Queues q, StepParams sp,
+                                                                                      unsigned long long* stats) {
   int ncross = 0, nhits = 0;
-  track_queue<NG, MORT>(m, P, q.trk_p, q.trk_x, q.trk_m, q.counters + 2, q.counters[1], sp.max_cross, ncross, nhits);
+  track_queue<NG, MORT>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], sp.max_cross, ncross, nhits);
   wave_add(stats + ST_CROSS * kStatSlots, ncross);
   wave_add(stats + ST_HITS * kStatSlots, nhits);
 }
 
 __global__ void k_reset_counters(int32_t* c) {
-  if (threadIdx.x < 3) c[threadIdx.x] = 0;   // stragglers, tracking queue, its head
+  if (threadIdx.x < 2) c[threadIdx.x] = 0;   // stragglers, tracking queue
 }
 
 // Reference coordinates of the final positions along the element tasks of
@@ -717,7 +717,7 @@ size_t task_bytes() { return sizeof(Task); }
 hipError_t launch_finalize_elem(const MeshView& m, const Particles& P, const void* tasks, const int32_t* ntask, int tp,
                                 int64_t n, int warm, int32_t* counters, int32_t* list, unsigned long long* stats,
                                 hipStream_t s) {
-  Queues q{counters, list, nullptr, nullptr, nullptr};
+  Queues q{counters, list, nullptr, nullptr, nullptr, nullptr};
   k_reset_counters<<<1, 64, 0, s>>>(counters);
   const int64_t max_tasks = (int64_t)m.E + P.cap / tp + 1;
 #define FP_L(A, B)                                                                                         \
@@ -772,7 +772,7 @@ bool stage_uses_tasks(const StageLaunch& L) {
 template <int NN, int NG, typename UT, bool MIXED, bool MLP>
 static void run_stage(const StageLaunch& L, hipStream_t s) {
   const MeshView& m = L.m;
-  Queues q{L.counters, L.strag, L.trk_p, L.trk_x, L.trk_m};
+  Queues q{L.counters, L.strag, L.trk_p, L.trk_x, L.trk_m, L.trk_s};
   int64_t lane_blocks;
   auto rec = [&](int i) { if (L.ev[i]) hipEventRecord(L.ev[i], s); };
   if (MLP && L.sp.mlp_guess) {
@@ -808,10 +808,10 @@ static void run_stage(const StageLaunch& L, hipStream_t s) {
         m, nullptr, L.n, L.P, L.fl, L.sp, q, L.stats);
     rec(3);
   }
-  int64_t trk_blocks = std::max<int64_t>(1, std::min<int64_t>((L.n + 255) / 256, 1024));
+  const dim3 tg((unsigned)std::max<int64_t>(1, std::min<int64_t>((L.n + 63) / 64, 4096)));
   rec(4);
-  if (m.n_mortar > 0) k_track<NG, true><<<dim3((unsigned)trk_blocks), 256, 0, s>>>(m, L.P, q, L.sp, L.stats);
-  else k_track<NG, false><<<dim3((unsigned)trk_blocks), 256, 0, s>>>(m, L.P, q, L.sp, L.stats);
+  if (m.n_mortar > 0) k_track<NG, true><<<tg, 64, 0, s>>>(m, L.P, q, L.sp, L.stats);
+  else k_track<NG, false><<<tg, 64, 0, s>>>(m, L.P, q, L.sp, L.stats);
   rec(5);
 }
 
