@@ -48,7 +48,6 @@ struct fp_ctx {
   double dl_R = 0.0, dl_per[3] = {0, 0, 0}, dl_pad = 0.0;
   unsigned long long* dep_pad = nullptr;   // largest distance of a particle outside its element box
   float* mlp_rows = nullptr;   // per-row activations for MLP gradients
-  float* mlp_grad = nullptr;   // gradient + loss scratch
   int32_t *tcount = nullptr, *tstart = nullptr, *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
   void* tasks = nullptr;
   double* trk_x = nullptr;
@@ -244,7 +243,7 @@ void particle_offsets(int64_t cap, int64_t* off, size_t* total) {
 struct Layout {
   size_t X, faces, fext, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
       mlp_flag, mlp_h1, mlp_ctr, mlp_w, mlp_adam, mlp_order, mlp_bloss, dl_count, dl_start, dl_list, stats,
-      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, mlp_grad, tcount, tstart, tasks, qcnt,
+      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tcount, tstart, tasks, qcnt,
       strag, trk_p, trk_x, trk_m, trk_s, mlp_guess, part[2], total;
   size_t part_bytes;
 };
@@ -292,7 +291,6 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   // F (4 doubles), validity flag, FP32 normalisation sum, FP32 local position (float4)
   L.dep = take((size_t)std::max<int64_t>(cap, 1) * 7 * 8 + 16);
   L.mlp_rows = take((size_t)kMlpMaxBatch * kMlpRow * 4);
-  L.mlp_grad = take((size_t)(kMlpWeights + 64) * 4);
   size_t pc1 = (size_t)std::max<int64_t>(cap, 1);
   L.tcount = take((E + 1) * 4);
   L.tstart = take((E + 1) * 4);
@@ -748,7 +746,6 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   c->scratch_i32 = (int32_t*)(b + L.scratch);
   c->dep_buf = (double*)(b + L.dep);
   c->mlp_rows = (float*)(b + L.mlp_rows);
-  c->mlp_grad = (float*)(b + L.mlp_grad);
   c->tcount = (int32_t*)(b + L.tcount);
   c->tstart = (int32_t*)(b + L.tstart);
   c->tasks = (void*)(b + L.tasks);
@@ -1217,16 +1214,11 @@ int fp_mlp_train_epoch(fp_ctx* c, float* w, float* m, float* v, int64_t* t, cons
   if (!c || !w || !m || !v || !t || !in || !target || !order || n <= 0 || batch <= 0) return FP_EINVAL;
   if (!c->ws) return fail(c, FP_ESTATE, "fp_mlp_train_epoch: no workspace");
   if (batch > kMlpMaxBatch) return fail(c, FP_EINVAL, "fp_mlp_train_epoch: batch above 8192");
-  int64_t nw = fp_mlp_n_weights();
-  float* grad = c->mlp_grad;
-  float* lbuf = grad + nw;
-  int64_t nb = n / batch;
-  for (int64_t bi = 0; bi < nb; ++bi) {
-    HIPCHK(c, launch_mlp_loss_grad(w, batch, in, target, order + bi * batch, grad,
-                                   loss ? loss + bi : lbuf, c->mlp_rows, c->stream));
-    (*t)++;
-    HIPCHK(c, launch_adam(w, m, v, grad, nw, *t, lr, c->stream));
-  }
+  const int64_t nb = n / batch;
+  if (loss) HIPCHK(c, launch_mlp_zero(loss, nb, c->stream));
+  for (int64_t bi = 0; bi < nb; ++bi)
+    HIPCHK(c, launch_mlp_train_step(w, m, v, ++*t, lr, batch, in, target, order + bi * batch,
+                                    loss ? loss + bi : nullptr, c->mlp_rows, c->stream));
   return FP_OK;
 }
 
@@ -1278,12 +1270,10 @@ int fp_mlp_train(fp_ctx* c, const float* in, const float* target, int64_t n, int
     // the previous epoch's copy of `order` must be done before it is reused
     HIPCHK(c, hipStreamSynchronize(s));
     HIPCHK(c, hipMemcpyAsync(c->mlp_order, order.data(), n * 4, hipMemcpyHostToDevice, s));
-    for (int64_t bi = 0; bi < nb; ++bi) {
-      HIPCHK(c, launch_mlp_loss_grad(w_out, batch, in, target, c->mlp_order + bi * batch, c->mlp_grad,
-                                     c->mlp_bloss + bi, c->mlp_rows, s));
-      ++t;
-      HIPCHK(c, launch_adam(w_out, c->mlp_adam, c->mlp_adam + nw, c->mlp_grad, nw, t, lr, s));
-    }
+    HIPCHK(c, launch_mlp_zero(c->mlp_bloss, nb, s));
+    for (int64_t bi = 0; bi < nb; ++bi)
+      HIPCHK(c, launch_mlp_train_step(w_out, c->mlp_adam, c->mlp_adam + nw, ++t, lr, batch, in, target,
+                                      c->mlp_order + bi * batch, c->mlp_bloss + bi, c->mlp_rows, s));
     if (loss_hist) {
       HIPCHK(c, hipMemcpyAsync(bl.data(), c->mlp_bloss, nb * 4, hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));

@@ -342,50 +342,6 @@ __device__ void mlp_features(const MeshView& m, int e, const double* x, float* f
   for (int r = 0; r < 3; ++r) feat[81 + r] = (float)((x[r] - ctr[r]) * ih);
 }
 
-__device__ __forceinline__ float fast_tanh(float s) { return tanhf(s); }
-
-// 84-64-64-64-3 forward for one row; weights read through the scalar path
-// (uniform addresses).
-__device__ inline void mlp_forward_row(const float* __restrict__ w, const float* in, float* out) {
-  constexpr int H = 64, NI = kMlpIn;
-  const float* W1 = w;
-  const float* b1 = W1 + H * NI;
-  const float* W2 = b1 + H;
-  const float* b2 = W2 + H * H;
-  const float* W3 = b2 + H;
-  const float* b3 = W3 + H * H;
-  const float* W4 = b3 + H;
-  const float* b4 = W4 + 3 * H;
-  float h1[H], h2[H];
-#pragma unroll 4
-  for (int o = 0; o < H; ++o) {
-    float s = b1[o];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) s += W1[o * NI + i] * in[i];
-    h1[o] = fast_tanh(s);
-  }
-#pragma unroll 2
-  for (int o = 0; o < H; ++o) {
-    float s = b2[o];
-#pragma unroll
-    for (int i = 0; i < H; ++i) s += W2[o * H + i] * h1[i];
-    h2[o] = fast_tanh(s);
-  }
-#pragma unroll 2
-  for (int o = 0; o < H; ++o) {
-    float s = b3[o];
-#pragma unroll
-    for (int i = 0; i < H; ++i) s += W3[o * H + i] * h2[i];
-    h1[o] = fast_tanh(s);
-  }
-  for (int o = 0; o < 3; ++o) {
-    float s = b4[o];
-#pragma unroll
-    for (int i = 0; i < H; ++i) s += W4[o * H + i] * h1[i];
-    out[o] = s;
-  }
-}
-
 // Reference coordinates of x in element e: the continued coordinates of the
 // particle's previous position (gw, may be null), then the learned guess
 // (flagged elements; gin, the stage's precomputed guess of this particle),

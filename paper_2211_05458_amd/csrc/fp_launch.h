@@ -93,8 +93,12 @@ hipError_t launch_mlp_loss_grad(const float* w, int64_t n, const float* in, cons
 // device address of the fixed row buffer of fp_mlp_loss_grad_static on the
 // current device (kMlpStaticRows rows)
 hipError_t mlp_static_rows(float** out);
-hipError_t launch_adam(float* w, float* m, float* v, const float* g, int64_t nw, int64_t t, float lr,
-                       hipStream_t s);
+// one step of minibatch Adam on n rows; *loss (may be null, cleared by the
+// caller) receives the batch's mean squared error
+hipError_t launch_mlp_train_step(float* w, float* m, float* v, int64_t t, float lr, int64_t n, const float* in,
+                                 const float* target, const int32_t* rows, float* loss, float* rowbuf,
+                                 hipStream_t s);
+hipError_t launch_mlp_zero(float* a, int64_t n, hipStream_t s);
 hipError_t launch_curved_flags(const MeshView& m, double thresh, uint8_t* flag, int32_t* count, hipStream_t s);
 hipError_t launch_mlp_elem_table(const MeshView& m, const float* w, float* h1, double* ctr, hipStream_t s);
 

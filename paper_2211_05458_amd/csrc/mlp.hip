@@ -1,6 +1,7 @@
 // Learned Newton initial guess: features, training pairs from Newton, a
 // 84-64-64-64-3 tanh MLP (forward, backward, Adam) in FP32, and the flags of
 // strongly curved elements on which the guess is used.
+#include <algorithm>
 #include <mutex>
 
 #include "fp_device.h"
@@ -73,206 +74,165 @@ __global__ void k_curved_flags(MeshView m, double thresh, uint8_t* flag, int32_t
   if (fl) atomicAdd(count, 1);
 }
 
-__global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ w, int64_t n,
-                                                     const float* __restrict__ in, float* out) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  float x[NI], o[3];
-  for (int i = 0; i < NI; ++i) x[i] = in[r * NI + i];
-  mlp_forward_row(w, x, o);
-  for (int k = 0; k < 3; ++k) out[r * 3 + k] = o[k];
-}
-
 // ---------------------------------------------------------------------------
-// Training on the matrix cores (FP32, v_mfma_f32_16x16x4f32).  The network
-// runs transposed, units as rows and batch rows as columns: a layer's 16x16
-// output tile holds, in lane (row l % 16, group q = l / 16), units
-// 16 t + 4 q + i in register i.  Taking the k-steps of the next product as the
-// unit sets {16 t + 4 k + i : k = 0..3} (k = lane group), register i of that
-// tile is already the B operand, forward (W H^T) and backward (W^T dZ^T)
-// alike; the weights are the A operands, read from LDS.
+// The FP32 network on the matrix cores (v_mfma_f32_16x16x4f32), transposed:
+// units as rows and batch rows as columns.  A workgroup of four wavefronts
+// takes 16 batch rows, each wavefront 16 of the 64 units of every layer; the
+// activations and deltas pass between the wavefronts through LDS.
+//
+// A training batch (1024 rows) is a chain of six dependent layers, so its time
+// is latency: one wavefront per 32 rows, which staged all 14 147 weights in LDS
+// first, left 32 wavefronts on the chip and took 86 us; here the weight
+// fragments of all layers are loaded into registers at once (about 90 per
+// lane), 256 wavefronts share the layers, and the pass takes 14.6 us.  The
+// weight gradients and Adam's update run in one kernel (k_mlp_wgrad), 16
+// wavefronts per 16x16 gradient tile.
+//
 // Lane layout: A[m][k], B[k][n] in lane (m or n) + 16 k; D[m][n] in lane
 // n + 16 (m / 4), register m % 4.
 // ---------------------------------------------------------------------------
 typedef float v4f32 __attribute__((ext_vector_type(4)));
 
-constexpr int FBT = 2;   // 16-row tiles per wavefront of the training pass
+constexpr int kW1 = 0, kB1 = H * NI, kW2 = kB1 + H, kB2 = kW2 + H * H, kW3 = kB2 + H, kB3 = kW3 + H * H, kW4 = kB3 + H,
+              kB4 = kW4 + NO * H;
+constexpr int kRowTile = 16;        // batch rows per workgroup
+constexpr int kActStride = H + 4;   // LDS row of one batch row's activations
 
-// forward and backward of 16 FBT batch rows per wavefront (one per workgroup);
-// activations and deltas to buf[row][ROW] (x, h1, h2, h3, d1, d2, d3, dy), the
-// mean squared error to *loss
-__global__ __launch_bounds__(64) void k_mlp_fb(const float* __restrict__ w, int64_t n, const float* __restrict__ in,
-                                               const float* __restrict__ target, const int32_t* __restrict__ rows,
-                                               float* buf, float* loss) {
-  __shared__ float W[NW];
-  for (int i = threadIdx.x; i < NW; i += 64) W[i] = w[i];
-  __syncthreads();
-  const float* W1 = W;
-  const float* b1 = W1 + H * NI;
-  const float* W2 = b1 + H;
-  const float* b2 = W2 + H * H;
-  const float* W3 = b2 + H;
-  const float* b3 = W3 + H * H;
-  const float* W4 = b3 + H;
-  const float* b4 = W4 + NO * H;
-  const int lane = threadIdx.x, kq = lane >> 4, col = lane & 15;
-  const int64_t r0 = (int64_t)blockIdx.x * (16 * FBT);
-  const float scale = 1.0f / (float)(n * NO);
-  int64_t src[FBT];
-  bool ok[FBT];
+// one layer of 64 inputs: units 16 wave .. + 15 of the 16 rows in `act`
+__device__ __forceinline__ v4f32 layer64(const float (*act)[kActStride], const float* a, v4f32 acc, int kq, int col) {
 #pragma unroll
-  for (int nt = 0; nt < FBT; ++nt) {
-    const int64_t r = r0 + 16 * nt + col;
-    ok[nt] = r < n;
-    src[nt] = ok[nt] ? (rows ? rows[r] : r) : 0;
-  }
-  // layer 1: k-steps of four consecutive inputs 4 s + k
-  v4f32 h1[4][FBT], h2[4][FBT], h3[4][FBT];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < FBT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h1[mt][nt][i] = b1[16 * mt + 4 * kq + i];
-#pragma unroll 3
-  for (int st = 0; st < NI / 4; ++st) {
-    float xb[FBT];
-#pragma unroll
-    for (int nt = 0; nt < FBT; ++nt) {
-      xb[nt] = ok[nt] ? in[src[nt] * NI + 4 * st + kq] : 0.f;
-      if (ok[nt]) buf[(r0 + 16 * nt + col) * ROW + 4 * st + kq] = xb[nt];
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const float a = W1[(16 * mt + col) * NI + 4 * st + kq];
-#pragma unroll
-      for (int nt = 0; nt < FBT; ++nt) h1[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xb[nt], h1[mt][nt], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < FBT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h1[mt][nt][i] = tanhf(h1[mt][nt][i]);
-  // hidden layers: k-step (t, i) = units 16 t + 4 k + i
-  auto forward = [&](const float* Wl, const float* bl, v4f32 (*hin)[FBT], v4f32 (*hout)[FBT]) {
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-      for (int nt = 0; nt < FBT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) hout[mt][nt][i] = bl[16 * mt + 4 * kq + i];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float a = Wl[(16 * mt + col) * H + 16 * t + 4 * kq + i];
-#pragma unroll
-          for (int nt = 0; nt < FBT; ++nt)
-            hout[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, hin[t][nt][i], hout[mt][nt], 0, 0, 0);
-        }
-#pragma unroll
-      for (int nt = 0; nt < FBT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) hout[mt][nt][i] = tanhf(hout[mt][nt][i]);
-    }
-  };
-  forward(W2, b2, h1, h2);
-  forward(W3, b3, h2, h3);
-  // output rows 0..2 (lanes of group 0, register j), error and its gradient
-  float lsum = 0.f;
-  float dyv[FBT][NO];
-#pragma unroll
-  for (int nt = 0; nt < FBT; ++nt) {
-    v4f32 y;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = (kq == 0 && i < NO) ? b4[i] : 0.f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float a = col < NO ? W4[col * H + 16 * t + 4 * kq + i] : 0.f;
-        y = __builtin_amdgcn_mfma_f32_16x16x4f32(a, h3[t][nt][i], y, 0, 0, 0);
-      }
-#pragma unroll
-    for (int j = 0; j < NO; ++j) {
-      float g = 0.f;
-      if (kq == 0 && ok[nt]) {
-        const float diff = y[j] - target[src[nt] * NO + j];
-        lsum += diff * diff * scale;
-        g = 2.0f * diff * scale;
-      }
-      dyv[nt][j] = g;
-    }
-  }
-  // d3 = W4^T dy (k = output j, one k-step) * (1 - h3^2)
-  v4f32 d3[4][FBT], d2[4][FBT], d1[4][FBT];
-#pragma unroll
-  for (int nt = 0; nt < FBT; ++nt) {
-    const float s0 = __shfl(dyv[nt][0], col, 64), s1 = __shfl(dyv[nt][1], col, 64), s2 = __shfl(dyv[nt][2], col, 64);
-    const float bdy = kq == 0 ? s0 : kq == 1 ? s1 : kq == 2 ? s2 : 0.f;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const float a = kq < NO ? W4[kq * H + 16 * mt + col] : 0.f;
-      v4f32 z = {0.f, 0.f, 0.f, 0.f};
-      z = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bdy, z, 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) d3[mt][nt][i] = z[i] * (1.f - h3[mt][nt][i] * h3[mt][nt][i]);
-    }
-    if (kq == 0 && ok[nt]) {
-#pragma unroll
-      for (int j = 0; j < NO; ++j) buf[(r0 + 16 * nt + col) * ROW + NI + 6 * H + j] = dyv[nt][j];
-    }
-  }
-  // d_prev = W^T d (A[m = input unit][k = output unit]) * (1 - h_prev^2)
-  auto backward = [&](const float* Wl, v4f32 (*din)[FBT], v4f32 (*hprev)[FBT], v4f32 (*dout)[FBT]) {
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      v4f32 z[FBT];
-#pragma unroll
-      for (int nt = 0; nt < FBT; ++nt) z[nt] = (v4f32){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float a = Wl[(16 * t + 4 * kq + i) * H + 16 * mt + col];
-#pragma unroll
-          for (int nt = 0; nt < FBT; ++nt) z[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, din[t][nt][i], z[nt], 0, 0, 0);
-        }
-#pragma unroll
-      for (int nt = 0; nt < FBT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dout[mt][nt][i] = z[nt][i] * (1.f - hprev[mt][nt][i] * hprev[mt][nt][i]);
-    }
-  };
-  backward(W3, d3, h2, d2);
-  backward(W2, d2, h1, d1);
-  // rows to the buffer: four consecutive units per lane and tile
-#pragma unroll
-  for (int nt = 0; nt < FBT; ++nt) {
-    if (!ok[nt]) continue;
-    float* B = buf + (r0 + 16 * nt + col) * ROW + NI;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int u = 16 * mt + 4 * kq;
-      *(float4*)(B + 0 * H + u) = make_float4(h1[mt][nt][0], h1[mt][nt][1], h1[mt][nt][2], h1[mt][nt][3]);
-      *(float4*)(B + 1 * H + u) = make_float4(h2[mt][nt][0], h2[mt][nt][1], h2[mt][nt][2], h2[mt][nt][3]);
-      *(float4*)(B + 2 * H + u) = make_float4(h3[mt][nt][0], h3[mt][nt][1], h3[mt][nt][2], h3[mt][nt][3]);
-      *(float4*)(B + 3 * H + u) = make_float4(d1[mt][nt][0], d1[mt][nt][1], d1[mt][nt][2], d1[mt][nt][3]);
-      *(float4*)(B + 4 * H + u) = make_float4(d2[mt][nt][0], d2[mt][nt][1], d2[mt][nt][2], d2[mt][nt][3]);
-      *(float4*)(B + 5 * H + u) = make_float4(d3[mt][nt][0], d3[mt][nt][1], d3[mt][nt][2], d3[mt][nt][3]);
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
-  if (lane == 0) atomicAdd(loss, lsum);
+  for (int s = 0; s < H / 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], act[col][4 * s + kq], acc, 0, 0, 0);
+  return acc;
 }
 
-// Weight and bias gradients on the matrix cores: one wavefront per 16x16
-// tile of a layer's gradient, summing over the batch rows (k-steps of four
-// rows): dW[o][i] = sum_r d[r][o] h_in[r][i]; the bias column is the tile whose
-// input is 1 in column 0.
+__device__ __forceinline__ void put_act(float (*act)[kActStride], int wave, int kq, int col, v4f32 h) {
+  *(float4*)&act[col][16 * wave + 4 * kq] = make_float4(h[0], h[1], h[2], h[3]);
+}
+
+// forward and, with BACK, backward of 16 batch rows at a time; BACK: activations
+// and deltas to buf[row][ROW] (x, h1, h2, h3, d1, d2, d3, dy) and the mean
+// squared error added to *loss (may be null); else the outputs to out[row][3].
+// A workgroup keeps its weights over all its row tiles.
+template <bool BACK>
+__global__ __launch_bounds__(256) void k_mlp_rows(const float* __restrict__ w, int64_t n, const float* __restrict__ in,
+                                                  const float* __restrict__ target, const int32_t* __restrict__ rows,
+                                                  float* __restrict__ buf, float* loss, float* __restrict__ out) {
+  __shared__ float sa[kRowTile][kActStride], sb[kRowTile][kActStride];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4, col = lane & 15;
+  const int unit = 16 * wave + col;   // row of the A operands
+  // this lane's fragments of every layer
+  float a1[NI / 4], a2[H / 4], a3[H / 4], a4[H / 4], t2[H / 4], t3[H / 4], t4 = 0.f;
+#pragma unroll
+  for (int s = 0; s < NI / 4; ++s) a1[s] = w[kW1 + unit * NI + 4 * s + kq];
+#pragma unroll
+  for (int s = 0; s < H / 4; ++s) {
+    a2[s] = w[kW2 + unit * H + 4 * s + kq];
+    a3[s] = w[kW3 + unit * H + 4 * s + kq];
+    a4[s] = col < NO ? w[kW4 + col * H + 4 * s + kq] : 0.f;
+    if (BACK) {
+      t2[s] = w[kW2 + (4 * s + kq) * H + unit];
+      t3[s] = w[kW3 + (4 * s + kq) * H + unit];
+    }
+  }
+  if (BACK && kq < NO) t4 = w[kW4 + kq * H + unit];
+  v4f32 b1, b2, b3, b4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int u = 16 * wave + 4 * kq + i;
+    b1[i] = w[kB1 + u];
+    b2[i] = w[kB2 + u];
+    b3[i] = w[kB3 + u];
+    b4[i] = (kq == 0 && i < NO) ? w[kB4 + i] : 0.f;
+  }
+  for (int64_t r0 = (int64_t)blockIdx.x * kRowTile; r0 < n; r0 += (int64_t)gridDim.x * kRowTile) {
+    const int64_t r = r0 + col;
+    const bool ok = r < n;
+    const int64_t src = ok ? (rows ? (int64_t)rows[r] : r) : 0;
+    float x[NI / 4], tg[NO] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NI / 4; ++s) x[s] = in[src * NI + 4 * s + kq];
+    if (BACK)
+#pragma unroll
+      for (int j = 0; j < NO; ++j) tg[j] = target[src * NO + j];
+    v4f32 h1 = b1;
+#pragma unroll
+    for (int s = 0; s < NI / 4; ++s) h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[s], x[s], h1, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h1[i] = tanhf(h1[i]);
+    put_act(sa, wave, kq, col, h1);
+    __syncthreads();
+    v4f32 h2 = layer64(sa, a2, b2, kq, col);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h2[i] = tanhf(h2[i]);
+    put_act(sb, wave, kq, col, h2);
+    __syncthreads();
+    v4f32 h3 = layer64(sb, a3, b3, kq, col);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h3[i] = tanhf(h3[i]);
+    put_act(sa, wave, kq, col, h3);   // sa's last readers passed the barrier above
+    __syncthreads();
+    // output layer, in every wavefront: rows 0..2 in lanes 0..15, register j
+    const v4f32 y = layer64(sa, a4, b4, kq, col);
+    if (!BACK) {
+      if (wave == 0 && kq == 0 && ok)
+#pragma unroll
+        for (int j = 0; j < NO; ++j) out[r * NO + j] = y[j];
+    } else {
+      const float scale = 1.0f / (float)(n * NO);
+      float lsum = 0.f, dy[NO];
+#pragma unroll
+      for (int j = 0; j < NO; ++j) {
+        const float diff = (kq == 0 && ok) ? y[j] - tg[j] : 0.f;
+        lsum += diff * diff * scale;
+        dy[j] = 2.0f * diff * scale;
+      }
+      // d3 = W4^T dy (1 - h3^2), one k-step (k = output)
+      const float s0 = __shfl(dy[0], col, 64), s1 = __shfl(dy[1], col, 64), s2 = __shfl(dy[2], col, 64);
+      const float b = kq == 0 ? s0 : kq == 1 ? s1 : kq == 2 ? s2 : 0.f;
+      const v4f32 zero = {0.f, 0.f, 0.f, 0.f};
+      v4f32 d3 = __builtin_amdgcn_mfma_f32_16x16x4f32(t4, b, zero, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d3[i] *= 1.f - h3[i] * h3[i];
+      put_act(sb, wave, kq, col, d3);   // sb's last readers passed the barrier above
+      __syncthreads();
+      v4f32 d2 = layer64(sb, t3, zero, kq, col);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d2[i] *= 1.f - h2[i] * h2[i];
+      put_act(sa, wave, kq, col, d2);   // sa's last readers passed the barrier above
+      __syncthreads();
+      v4f32 d1 = layer64(sa, t2, zero, kq, col);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d1[i] *= 1.f - h1[i] * h1[i];
+      if (ok) {
+        float* B = buf + r * ROW;
+        if (wave == 0) {
+#pragma unroll
+          for (int s = 0; s < NI / 4; ++s) B[4 * s + kq] = x[s];
+          if (kq == 0)
+#pragma unroll
+            for (int j = 0; j < NO; ++j) B[NI + 6 * H + j] = dy[j];
+        }
+        // four consecutive units per lane and layer
+        B += NI + 16 * wave + 4 * kq;
+        const v4f32 v[6] = {h1, h2, h3, d1, d2, d3};
+#pragma unroll
+        for (int l = 0; l < 6; ++l)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) B[l * H + i] = v[l][i];
+      }
+      if (wave == 0 && loss) {
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+        if (lane == 0) atomicAdd(loss, lsum);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Weight and bias gradients on the matrix cores: one workgroup per 16x16 tile
+// of a layer's gradient, dW[o][i] = sum_r d[r][o] h_in[r][i]; the bias column
+// is the tile whose input is 1 in column 0.
 struct GradTile { int layer, mt, it; };   // it == -1: the bias tile
 __device__ inline GradTile grad_tile(int b) {
   // layer 1: 4 x 6 tiles (84 inputs) + 4 bias tiles; layers 2, 3: 4 x 4 + 4;
@@ -287,10 +247,29 @@ __device__ inline GradTile grad_tile(int b) {
 }
 constexpr int kGradTiles = 28 + 20 + 20 + 5;
 
-// four wavefronts per tile, each summing every fourth group of four rows,
-// then the four partial tiles added in a fixed order
-__global__ __launch_bounds__(256) void k_mlp_wgrad_mfma(int64_t n, const float* __restrict__ buf, float* grad) {
-  __shared__ v4f32 part[3][64];
+struct AdamState {
+  float *w, *m, *v;   // updated in place
+  float lr, c1, c2;   // step and bias corrections 1 - beta^t
+};
+
+__device__ __forceinline__ void adam(float* w, float* m, float* v, float g, float lr, float c1, float c2) {
+  const float mi = 0.9f * *m + 0.1f * g, vi = 0.999f * *v + 0.001f * g * g;
+  *m = mi;
+  *v = vi;
+  *w -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+}
+
+// The wavefronts of a tile take every 16th group of four rows (four groups in
+// flight) and their partial tiles are added in a fixed order.  With four
+// wavefronts per tile a batch of 1024 rows was 16 dependent rounds of loads
+// (12.8 us, and Adam 4.8 us in a launch of its own); 16 wavefronts need four
+// (7.1 us with Adam).
+// ADAM: the gradient goes straight into Adam's update; else to grad.
+constexpr int kGradWaves = 16;
+template <bool ADAM>
+__global__ __launch_bounds__(64 * kGradWaves) void k_mlp_wgrad(int64_t n, const float* __restrict__ buf, float* grad,
+                                                               AdamState ad) {
+  __shared__ v4f32 part[kGradWaves][64];
   const GradTile T = grad_tile(blockIdx.x);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = lane >> 4, col = lane & 15;
   const int nin = T.layer == 0 ? NI : H, nout = T.layer == 3 ? NO : H;
@@ -301,11 +280,11 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad_mfma(int64_t n, const float* 
   const bool ao = o < nout, bi = T.it >= 0 && i < nin;
   v4f32 acc = {0.f, 0.f, 0.f, 0.f};
   constexpr int U = 4;   // k-steps in flight
-  for (int64_t r0 = 4 * (int64_t)wv; r0 < n; r0 += 16 * U) {
+  for (int64_t r0 = 4 * (int64_t)wv; r0 < n; r0 += 4 * kGradWaves * U) {
     float a[U], b[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t r = r0 + 16 * u + kq;
+      const int64_t r = r0 + 4 * kGradWaves * u + kq;
       const bool live = r < n;
       const float* B = buf + (live ? r : 0) * ROW;
       a[u] = (ao && live) ? B[d_off + o] : 0.f;
@@ -314,40 +293,32 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad_mfma(int64_t n, const float* 
 #pragma unroll
     for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u], acc, 0, 0, 0);
   }
-  if (wv > 0) part[wv - 1][lane] = acc;
+  part[wv][lane] = acc;
   __syncthreads();
-  if (wv != 0) return;
-  acc += part[0][lane];
-  acc += part[1][lane];
-  acc += part[2][lane];
-  // D[m = output 16 mt + 4 kq + j][n = input col]
+  // 256 threads, one gradient each: register j of lane ln
+  if (threadIdx.x >= 256) return;
+  const int ln = threadIdx.x >> 2, j = threadIdx.x & 3;
+  float g = 0.f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int oo = 16 * T.mt + 4 * kq + j;
-    if (oo >= nout) continue;
-    if (T.it >= 0) {
-      if (bi) grad[wofs + (size_t)oo * nin + i] = acc[j];
-    } else if (col == 0) {
-      grad[wofs + (size_t)nout * nin + oo] = acc[j];
-    }
+  for (int k = 0; k < kGradWaves; ++k) g += part[k][ln][j];
+  // D[m = output 16 mt + 4 (ln / 16) + j][n = input ln % 16]
+  const int oo = 16 * T.mt + 4 * (ln >> 4) + j, ii = 16 * T.it + (ln & 15);
+  if (oo >= nout) return;
+  size_t at;
+  if (T.it >= 0) {
+    if (ii >= nin) return;
+    at = wofs + (size_t)oo * nin + ii;
+  } else {
+    if ((ln & 15) != 0) return;
+    at = wofs + (size_t)nout * nin + oo;
   }
+  if (ADAM) adam(ad.w + at, ad.m + at, ad.v + at, g, ad.lr, ad.c1, ad.c2);
+  else grad[at] = g;
 }
 
 __global__ void k_zero_f32(float* a, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = 0.0f;
-}
-
-__global__ void k_adam(float* w, float* m, float* v, const float* __restrict__ g, int64_t nw, float lr, float c1,
-                       float c2) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw) return;
-  float gi = g[i];
-  float mi = 0.9f * m[i] + 0.1f * gi;
-  float vi = 0.999f * v[i] + 0.001f * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
 }
 
 hipError_t launch_mlp_features(const MeshView& m, int64_t n, const int32_t* elem, const double* x, float* feat,
@@ -622,9 +593,13 @@ hipError_t launch_mlp_guess(const MeshView& m, const Particles& P, int64_t n, in
   return hipGetLastError();
 }
 
+static dim3 row_tiles(int64_t n) { return dim3((unsigned)((n + kRowTile - 1) / kRowTile)); }
+
 hipError_t launch_mlp_forward(const float* w, int64_t n, const float* in, float* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_mlp_forward<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(w, n, in, out);
+  // at most four workgroups per CU, each keeping its weights over its row tiles
+  const dim3 g(std::min(row_tiles(n).x, 1024u));
+  k_mlp_rows<false><<<g, 256, 0, s>>>(w, n, in, nullptr, nullptr, nullptr, nullptr, out);
   return hipGetLastError();
 }
 
@@ -659,18 +634,28 @@ hipError_t mlp_static_rows(float** out) {
   return hipSuccess;
 }
 
+hipError_t launch_mlp_zero(float* a, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  k_zero_f32<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(a, n);
+  return hipGetLastError();
+}
+
 hipError_t launch_mlp_loss_grad(const float* w, int64_t n, const float* in, const float* target,
                                 const int32_t* rows, float* grad, float* loss, float* rowbuf, hipStream_t s) {
   if (n <= 0 || n > kMlpMaxBatch) return hipErrorInvalidValue;
   k_zero_f32<<<1, 64, 0, s>>>(loss, 1);
-  k_mlp_fb<<<dim3((unsigned)((n + 16 * FBT - 1) / (16 * FBT))), 64, 0, s>>>(w, n, in, target, rows, rowbuf, loss);
-  k_mlp_wgrad_mfma<<<dim3(kGradTiles), 256, 0, s>>>(n, rowbuf, grad);
+  k_mlp_rows<true><<<row_tiles(n), 256, 0, s>>>(w, n, in, target, rows, rowbuf, loss, nullptr);
+  k_mlp_wgrad<false><<<dim3(kGradTiles), 64 * kGradWaves, 0, s>>>(n, rowbuf, grad, AdamState{});
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float* w, float* m, float* v, const float* g, int64_t nw, int64_t t, float lr, hipStream_t s) {
-  float c1 = 1.0f - powf(0.9f, (float)t), c2 = 1.0f - powf(0.999f, (float)t);
-  k_adam<<<dim3((unsigned)((nw + 255) / 256)), 256, 0, s>>>(w, m, v, g, nw, lr, c1, c2);
+hipError_t launch_mlp_train_step(float* w, float* m, float* v, int64_t t, float lr, int64_t n, const float* in,
+                                 const float* target, const int32_t* rows, float* loss, float* rowbuf,
+                                 hipStream_t s) {
+  if (n <= 0 || n > kMlpMaxBatch) return hipErrorInvalidValue;
+  const AdamState ad{w, m, v, lr, 1.0f - powf(0.9f, (float)t), 1.0f - powf(0.999f, (float)t)};
+  k_mlp_rows<true><<<row_tiles(n), 256, 0, s>>>(w, n, in, target, rows, rowbuf, loss, nullptr);
+  k_mlp_wgrad<true><<<dim3(kGradTiles), 64 * kGradWaves, 0, s>>>(n, rowbuf, nullptr, ad);
   return hipGetLastError();
 }
 
