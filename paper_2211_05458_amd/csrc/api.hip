@@ -48,7 +48,7 @@ struct fp_ctx {
   double dl_R = 0.0, dl_per[3] = {0, 0, 0}, dl_pad = 0.0;
   unsigned long long* dep_pad = nullptr;   // largest distance of a particle outside its element box
   float* mlp_rows = nullptr;   // per-row activations for MLP gradients
-  int32_t *tcount = nullptr, *tstart = nullptr, *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
+  int32_t *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
   void* tasks = nullptr;
   double* trk_x = nullptr;
   uint8_t* trk_m = nullptr;
@@ -224,6 +224,12 @@ struct Timed {
   }
 };
 
+// the device counters qcnt: a pair of queue counters per stage (stage i clears
+// stage i + 1's, the last one stage 0's, so that every step begins alike), the
+// number of element tasks, the list lengths of the final locate and of the
+// learned guess
+enum { kCntTasks = 10, kCntLocate = 12, kCntGuess = 13 };
+
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Byte offsets of the particle arrays in one block of capacity cap (the
@@ -243,7 +249,7 @@ void particle_offsets(int64_t cap, int64_t* off, size_t* total) {
 struct Layout {
   size_t X, faces, fext, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
       mlp_flag, mlp_h1, mlp_ctr, mlp_w, mlp_adam, mlp_order, mlp_bloss, dl_count, dl_start, dl_list, stats,
-      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tcount, tstart, tasks, qcnt,
+      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tasks, qcnt,
       strag, trk_p, trk_x, trk_m, trk_s, mlp_guess, part[2], total;
   size_t part_bytes;
 };
@@ -292,8 +298,6 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   L.dep = take((size_t)std::max<int64_t>(cap, 1) * 7 * 8 + 16);
   L.mlp_rows = take((size_t)kMlpMaxBatch * kMlpRow * 4);
   size_t pc1 = (size_t)std::max<int64_t>(cap, 1);
-  L.tcount = take((E + 1) * 4);
-  L.tstart = take((E + 1) * 4);
   L.tasks = take((E + pc1 / kMinTaskParticles + 2) * task_bytes());
   L.qcnt = take(64);
   L.strag = take(pc1 * 4);
@@ -447,12 +451,10 @@ int sort_particles(fp_ctx* c, int tp) {
     return FP_OK;
   }
   HIPCHK(c, launch_sort(c->P[c->cur], c->P[1 - c->cur], c->np, c->E, c->sort_count, c->sort_start, c->sort_rank,
-                        c->sort_sums, s));
+                        c->sort_sums, tp, c->tasks, c->qcnt + kCntTasks, (int64_t)c->E + c->cap / tp + 2, s));
   c->cur = 1 - c->cur;
   c->sorts++;
   c->sorted_fresh = true;
-  HIPCHK(c, launch_tasks(c->sort_count, c->sort_start, c->E, tp, c->tcount, c->tstart, c->sort_sums, c->tasks,
-                         c->qcnt + 4, (int64_t)c->E + c->cap / tp + 2, s));
   c->tasks_valid = true;
   c->task_tp = tp;
   return FP_OK;
@@ -460,22 +462,7 @@ int sort_particles(fp_ctx* c, int tp) {
 
 int sync_bound(fp_ctx* c) {
   if (!c->bound || c->cur == 0 || c->np == 0) return FP_OK;
-  const Particles& S = c->P[1];
-  const Particles& D = c->P[0];
-  const size_t n = (size_t)c->np;
-  hipStream_t s = c->stream;
-  for (int k = 0; k < 3; ++k) {
-    HIPCHK(c, hipMemcpyAsync(D.x + k * D.cap, S.x + k * S.cap, n * 8, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(D.v + k * D.cap, S.v + k * S.cap, n * 8, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(D.kx + k * D.cap, S.kx + k * S.cap, n * 8, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(D.kv + k * D.cap, S.kv + k * S.cap, n * 8, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(D.xi + k * D.cap, S.xi + k * S.cap, n * 8, hipMemcpyDeviceToDevice, s));
-  }
-  HIPCHK(c, hipMemcpyAsync(D.d, S.d, n * 8, hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, hipMemcpyAsync(D.elem, S.elem, n * 4, hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, hipMemcpyAsync(D.hits, S.hits, n * 4, hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, hipMemcpyAsync(D.id, S.id, n * 4, hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, hipMemcpyAsync(D.status, S.status, n, hipMemcpyDeviceToDevice, s));
+  HIPCHK(c, launch_copy_particles(c->P[1], c->P[0], c->np, c->stream));
   c->cur = 0;
   return FP_OK;
 }
@@ -704,6 +691,8 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
     HIPCHK(c, hipMemcpyAsync(b + L.blist, c->blist.data(), c->blist.size() * 4, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipMemsetAsync(b + L.stats, 0, 16 * kStatSlots * 8, s));
   HIPCHK(c, hipMemsetAsync(b + L.mlp_flag, 0, E, s));
+  HIPCHK(c, hipMemsetAsync(b + L.sort_count, 0, (E + 1) * 4, s));
+  HIPCHK(c, hipMemsetAsync(b + L.qcnt, 0, 64, s));
   MeshView& m = c->mv;
   m = MeshView{};
   m.E = c->E; m.ng = c->ng; m.n = c->n; m.n_geo = c->n_geo;
@@ -746,8 +735,6 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   c->scratch_i32 = (int32_t*)(b + L.scratch);
   c->dep_buf = (double*)(b + L.dep);
   c->mlp_rows = (float*)(b + L.mlp_rows);
-  c->tcount = (int32_t*)(b + L.tcount);
-  c->tstart = (int32_t*)(b + L.tstart);
   c->tasks = (void*)(b + L.tasks);
   c->qcnt = (int32_t*)(b + L.qcnt);
   c->strag = (int32_t*)(b + L.strag);
@@ -934,8 +921,10 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
       Lc.mlp = sp.use_mlp;
       Lc.tasks = c->tasks_valid ? c->tasks : nullptr;
       Lc.task_tp = c->task_tp;
-      Lc.ntask = c->qcnt + 4;
-      Lc.counters = c->qcnt;
+      Lc.ntask = c->qcnt + kCntTasks;
+      Lc.counters = c->qcnt + 2 * i;
+      Lc.next_counters = c->qcnt + 2 * ((i + 1) % S);
+      Lc.guess_count = c->qcnt + kCntGuess;
       Lc.strag = c->strag;
       Lc.trk_p = c->trk_p;
       Lc.trk_x = c->trk_x;
@@ -977,7 +966,7 @@ static hipError_t finalize(fp_ctx* c, hipStream_t s) {
   const int warm = c->xi_warm ? 1 : 0;
   const Particles& P = c->P[c->cur];
   if (c->tasks_valid)
-    return launch_finalize_elem(c->mv, P, c->tasks, c->qcnt + 4, c->task_tp, c->np, warm, c->qcnt, c->strag,
+    return launch_finalize_elem(c->mv, P, c->tasks, c->qcnt + kCntTasks, c->task_tp, c->np, warm, c->qcnt + kCntLocate, c->strag,
                                 c->stats, s);
   return launch_finalize(c->mv, P, c->np, nullptr, nullptr, warm, c->stats, s);
 }
@@ -1049,7 +1038,7 @@ int fp_deposit_source(fp_ctx* c, void* S, fp_dtype dt, int32_t kind, double radi
                                      c->node_pad, c->dep_buf, c->sort_start, c->dep_pad,
                                      c->count_pairs ? c->stats + ST_DEP_PAIRS * kStatSlots : nullptr, c->dl_valid ? c->dl_start : nullptr,
                                      c->dl_list, c->dl_pad, c->rl_buf, c->rl_cap,
-                                     c->tasks_valid ? c->tasks : nullptr, c->qcnt + 4, c->task_tp, ev, c->stream));
+                                     c->tasks_valid ? c->tasks : nullptr, c->qcnt + kCntTasks, c->task_tp, ev, c->stream));
     }
     if (c->timing && ev[0] && ev[1] && ev[2] && ev[3]) {
       c->recs.push_back({7, ev[0], ev[1]});

@@ -123,6 +123,9 @@ __host__ __device__ constexpr int task_particles(int nn, int ng, bool mixed) {
 }
 constexpr int kMinTaskParticles = 32;
 
+// one element task of the stage kernels: particles p0 .. p0 + cnt of element e
+struct Task { int32_t e, p0, cnt, pad; };
+
 // extra terms of the equation of motion (eq. theory:maxey), bit flags
 constexpr int kForceBuoyancy = 1, kForceStress = 2, kForceAddedMass = 4, kForceSaffman = 8;
 constexpr int kForceAll = 15;

@@ -28,7 +28,9 @@ struct StageLaunch {
   const void* tasks;        // element tasks from the last sort, or null
   int task_tp;              // particles per task of those tasks
   const int32_t* ntask;
-  int32_t* counters;        // queue counters [2]
+  int32_t* counters;        // queue counters [2], zero at the start
+  int32_t* next_counters;   // [2], left zero for the next stage
+  int32_t* guess_count;     // length of the learned guess's list
   int32_t* strag;           // [cap]
   int32_t* trk_p;           // [cap]
   double* trk_x;            // [3][cap]
@@ -39,8 +41,6 @@ struct StageLaunch {
 };
 hipError_t launch_stage(const StageLaunch& L, hipStream_t s);
 bool stage_uses_tasks(const StageLaunch& L);   // k_stage_elem runs (else all particles go per lane)
-hipError_t launch_tasks(const int32_t* count, const int32_t* start, int E, int tp, int32_t* tcount, int32_t* tstart,
-                        int32_t* sums, void* tasks, int32_t* ntask, int64_t max_tasks, hipStream_t s);
 size_t task_bytes();
 hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* sums, hipStream_t s);
 hipError_t launch_finalize_elem(const MeshView& m, const Particles& P, const void* tasks, const int32_t* ntask, int tp,
@@ -73,9 +73,12 @@ inline size_t deposit_reuse_bytes(int E, int32_t cap) {
 hipError_t launch_dep_lists(const MeshView& m, double R, const double* period, double pad, int pass,
                             int32_t* count, const int32_t* start, int32_t* list, hipStream_t s);
 constexpr int kDepListPerElem = 256;   // workspace budget of candidate-list entries per element
-hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count,
-                       int32_t* start, int32_t* rank, int32_t* block_sums, hipStream_t s);
-hipError_t launch_elem_start(const Particles& P, int64_t n, int E, int32_t* elem_start, hipStream_t s);
+// counting sort of src into dst and the element tasks of tp particles each;
+// count (E + 1 entries) is zero before and after
+hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count, int32_t* start,
+                       int32_t* rank, int32_t* sums, int tp, void* tasks, int32_t* ntask, int64_t max_tasks,
+                       hipStream_t s);
+hipError_t launch_copy_particles(const Particles& S, const Particles& D, int64_t n, hipStream_t s);
 
 // learned guess
 hipError_t launch_mlp_features(const MeshView& m, int64_t n, const int32_t* elem, const double* x, float* feat,

@@ -1,14 +1,14 @@
 // Counting sort of the particle arrays by element (active particles first,
 // in element order; inactive ones at the end).  Histogram with atomics, an
-// exclusive scan over the E+1 buckets, then a scatter of every SoA field.
+// exclusive scan over the E+1 buckets that also writes the element tasks and
+// clears the histogram for the next sort, then a scatter of every SoA field.
+// Launches of a few microseconds each are what a sort of few particles costs:
+// clear, histogram, two three-launch scans, task count, task fill and scatter
+// were 11 of them (46 us for 1e4 particles); one scan of bucket starts and task
+// starts together leaves three, or four beyond kScanTile buckets.
 #include "fp_launch.h"
 
 namespace fp {
-
-__global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = v;
-}
 
 // rank of each particle within its bucket.  The particles are mostly in
 // element order already (sorted at the last step, few crossings since), so
@@ -131,16 +131,139 @@ hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* sums, h
   return hipGetLastError();
 }
 
+constexpr int kScanPer = 16, kScanTile = 256 * kScanPer;   // buckets per thread and per workgroup
+
+// exclusive prefix over the workgroup's 256 threads of two sums at once
+__device__ __forceinline__ void block_scan2(int& a, int& b, int* ta, int* tb) {
+  __shared__ int sa[4], sb[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x = a, y = b;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(x, o, 64), v = __shfl_up(y, o, 64);
+    if (lane >= o) { x += u; y += v; }
+  }
+  if (lane == 63) { sa[wave] = x; sb[wave] = y; }
+  __syncthreads();
+  int pa = 0, pb = 0;
+  *ta = *tb = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) { pa += sa[w]; pb += sb[w]; }
+    *ta += sa[w];
+    *tb += sb[w];
+  }
+  __syncthreads();
+  a = pa + x - a;
+  b = pb + y - b;
+}
+
+__device__ __forceinline__ int tasks_of(int count, int tp) { return (count + tp - 1) / tp; }
+
+// sums of each tile of buckets: particles and element tasks (bucket E, the
+// inactive particles, has no tasks)
+__global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ count, int E, int tp, int32_t* sums) {
+  const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+  int a = 0, b = 0, ta, tb;
+  for (int k = 0; k < kScanPer; ++k) {
+    const int64_t e = b0 + k * 256 + threadIdx.x;
+    const int c = e <= E ? count[e] : 0;
+    a += c;
+    if (e < E) b += tasks_of(c, tp);
+  }
+  block_scan2(a, b, &ta, &tb);
+  if (threadIdx.x == 0) {
+    sums[2 * blockIdx.x] = ta;
+    sums[2 * blockIdx.x + 1] = tb;
+  }
+}
+
+// bucket starts, the elements' tasks of at most tp particles and their number;
+// the histogram is cleared.  sums: every tile's sums (the workgroup adds those
+// before its own: a few hundred values for the largest meshes).
+__global__ __launch_bounds__(256) void k_sort_scan(int32_t* __restrict__ count, int32_t* __restrict__ start, int E,
+                                                   int tp, const int32_t* __restrict__ sums, Task* __restrict__ tasks,
+                                                   int32_t* ntask, int64_t max_tasks) {
+  int before = 0, tbefore = 0, ta, tb;
+  if (blockIdx.x > 0) {
+    int a = 0, b = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += 256) {
+      a += sums[2 * t];
+      b += sums[2 * t + 1];
+    }
+    block_scan2(a, b, &before, &tbefore);
+  }
+  const int64_t e0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
+  int c[kScanPer], a = 0, b = 0;
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    c[k] = e0 + k <= E ? count[e0 + k] : 0;
+    a += c[k];
+    if (e0 + k < E) b += tasks_of(c[k], tp);
+  }
+  block_scan2(a, b, &ta, &tb);
+  a += before;
+  b += tbefore;
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    const int64_t e = e0 + k;
+    if (e > E) break;
+    start[e] = a;
+    count[e] = 0;
+    if (e < E) {
+      for (int j = 0; j < c[k] && b < max_tasks; j += tp, ++b) {
+        Task t;
+        t.e = (int32_t)e;
+        t.p0 = a + j;
+        t.cnt = min(tp, c[k] - j);
+        t.pad = 0;
+        tasks[b] = t;
+      }
+    } else {
+      *ntask = b;
+    }
+    a += c[k];
+  }
+}
+
 hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count, int32_t* start,
-                       int32_t* rank, int32_t* block_sums, hipStream_t s) {
+                       int32_t* rank, int32_t* sums, int tp, void* tasks, int32_t* ntask, int64_t max_tasks,
+                       hipStream_t s) {
   if (n == 0) return hipSuccess;
-  int64_t nb = E + 1;
-  k_fill_i32<<<dim3((unsigned)((nb + 255) / 256)), 256, 0, s>>>(count, nb, 0);
-  k_sort_hist<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(src.status, src.elem, n, E, count, rank);
-  hipError_t err = scan_i32(count, start, nb, block_sums, s);
-  if (err != hipSuccess) return err;
-  k_sort_scatter<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(src, dst, n, E, start, rank);
+  const dim3 g((unsigned)((n + 255) / 256)), tiles((unsigned)((E + kScanTile) / kScanTile));   // E + 1 buckets
+  k_sort_hist<<<g, 256, 0, s>>>(src.status, src.elem, n, E, count, rank);
+  if (tiles.x > 1) k_sort_sums<<<tiles, 256, 0, s>>>(count, E, tp, sums);
+  k_sort_scan<<<tiles, 256, 0, s>>>(count, start, E, tp, sums, (Task*)tasks, ntask, max_tasks);
+  k_sort_scatter<<<g, 256, 0, s>>>(src, dst, n, E, start, rank);
   return hipGetLastError();
 }
+
+// the first n particles of S to the same rows of D (a caller-owned block)
+__global__ __launch_bounds__(256) void k_copy_particles(Particles S, Particles D, int64_t n) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const int64_t cs = S.cap, cd = D.cap;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    D.x[k * cd + p] = S.x[k * cs + p];
+    D.v[k * cd + p] = S.v[k * cs + p];
+    D.kx[k * cd + p] = S.kx[k * cs + p];
+    D.kv[k * cd + p] = S.kv[k * cs + p];
+    D.xi[k * cd + p] = S.xi[k * cs + p];
+  }
+  D.d[p] = S.d[p];
+  D.elem[p] = S.elem[p];
+  D.hits[p] = S.hits[p];
+  D.id[p] = S.id[p];
+  D.status[p] = S.status[p];
+}
+
+hipError_t launch_copy_particles(const Particles& S, const Particles& D, int64_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  k_copy_particles<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(S, D, n);
+  return hipGetLastError();
+}
+
+size_t task_bytes() { return sizeof(Task); }
 
 }  // namespace fp

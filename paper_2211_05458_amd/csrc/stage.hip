@@ -159,10 +159,9 @@ __device__ __forceinline__ void interp_f32_mfma(const MeshView& m, const float* 
   }
 }
 
-struct Task { int32_t e, p0, cnt, pad; };
-
 struct Queues {
   int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word)
+  int32_t* next;      // the next stage's counters
   int32_t* strag;     // [cap]
   int32_t* trk_p;     // [cap]
   double* trk_x;      // [3][cap] segment start
@@ -527,6 +526,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
                                                                                       Queues q, StepParams sp,
                                                                                       unsigned long long* stats) {
   int ncross = 0, nhits = 0;
+  // the next stage's counters, last read by the stage before this one
+  if (blockIdx.x == 0 && threadIdx.x < 2) q.next[threadIdx.x] = 0;
   track_queue<NG, MORT>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], sp.max_cross, ncross, nhits);
   wave_add(stats + ST_CROSS * kStatSlots, ncross);
   wave_add(stats + ST_HITS * kStatSlots, nhits);
@@ -674,50 +675,12 @@ __global__ void k_dep_clear(double* F, int32_t* ok, int64_t n) {
   ok[p] = 0;
 }
 
-// tasks of <= tp particles per element after the counting sort
-__global__ void k_task_count(const int32_t* __restrict__ count, int E, int tp, int32_t* tcount) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < E) tcount[e] = (count[e] + tp - 1) / tp;
-  else if (e == E) tcount[E] = 0;
-}
-
-__global__ void k_task_fill(const int32_t* __restrict__ count, const int32_t* __restrict__ start,
-                            const int32_t* __restrict__ tstart, int E, int tp, Task* tasks, int32_t* ntask,
-                            int64_t max_tasks) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= E) return;
-  int c = count[e], t0 = tstart[e], s0 = start[e];
-  for (int j = 0; tp * j < c && (int64_t)t0 + j < max_tasks; ++j) {
-    Task t;
-    t.e = e;
-    t.p0 = s0 + tp * j;
-    t.cnt = min(tp, c - tp * j);
-    t.pad = 0;
-    tasks[t0 + j] = t;
-  }
-  if (e == E - 1) *ntask = (int32_t)min((int64_t)tstart[E], max_tasks);
-}
-
-hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* sums, hipStream_t s);
-
-hipError_t launch_tasks(const int32_t* count, const int32_t* start, int E, int tp, int32_t* tcount, int32_t* tstart,
-                        int32_t* sums, void* tasks, int32_t* ntask, int64_t max_tasks, hipStream_t s) {
-  dim3 g((unsigned)((E + 1 + 255) / 256));
-  k_task_count<<<g, 256, 0, s>>>(count, E, tp, tcount);
-  hipError_t err = scan_i32(tcount, tstart, E + 1, sums, s);
-  if (err != hipSuccess) return err;
-  k_task_fill<<<g, 256, 0, s>>>(count, start, tstart, E, tp, (Task*)tasks, ntask, max_tasks);
-  return hipGetLastError();
-}
-
-size_t task_bytes() { return sizeof(Task); }
-
 #include "fp_shapes.h"
 
 hipError_t launch_finalize_elem(const MeshView& m, const Particles& P, const void* tasks, const int32_t* ntask, int tp,
                                 int64_t n, int warm, int32_t* counters, int32_t* list, unsigned long long* stats,
                                 hipStream_t s) {
-  Queues q{counters, list, nullptr, nullptr, nullptr, nullptr};
+  Queues q{counters, nullptr, list, nullptr, nullptr, nullptr, nullptr};
   k_reset_counters<<<1, 64, 0, s>>>(counters);
   const int64_t max_tasks = (int64_t)m.E + P.cap / tp + 1;
 #define FP_L(A, B)                                                                                         \
@@ -772,16 +735,15 @@ bool stage_uses_tasks(const StageLaunch& L) {
 template <int NN, int NG, typename UT, bool MIXED, bool MLP>
 static void run_stage(const StageLaunch& L, hipStream_t s) {
   const MeshView& m = L.m;
-  Queues q{L.counters, L.strag, L.trk_p, L.trk_x, L.trk_m, L.trk_s};
+  Queues q{L.counters, L.next_counters, L.strag, L.trk_p, L.trk_x, L.trk_m, L.trk_s};
   int64_t lane_blocks;
   auto rec = [&](int i) { if (L.ev[i]) hipEventRecord(L.ev[i], s); };
   if (MLP && L.sp.mlp_guess) {
-    // the straggler list and its counter hold the guess list until the reset
+    // the straggler list holds the guess list until the stage kernels run
     rec(6);
-    (void)launch_mlp_guess(m, L.P, L.n, L.sp.warm, L.strag, L.counters, const_cast<float*>(L.sp.mlp_guess), s);
+    (void)launch_mlp_guess(m, L.P, L.n, L.sp.warm, L.strag, L.guess_count, const_cast<float*>(L.sp.mlp_guess), s);
     rec(7);
   }
-  k_reset_counters<<<1, 64, 0, s>>>(L.counters);
   if (stage_uses_tasks(L)) {
     // at most E + cap / tp + 1 tasks, 64 / tp per wavefront
     constexpr int tp = task_particles(NN, NG, MIXED), nw = elem_waves(tp);
