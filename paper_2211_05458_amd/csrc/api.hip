@@ -889,7 +889,7 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
   sp.forces = o->forces;
   sp.mlp_guess = (sp.use_mlp && c->n_flagged > 0) ? c->mlp_guess : nullptr;
   hipStream_t s = c->stream;
-  const int tp = task_particles(c->n, c->ng, o->precision == 1);
+  const int tp = task_particles(c->n, c->ng, o->precision == 1, o->forces != 0);
   for (int st = 0; st < n_steps; ++st) {
     if (o->sort_every < 0 || (o->sort_every > 0 && (c->steps_done % o->sort_every) == 0)) {
       // a sort since the particles last moved (the shape-kernel source sorts

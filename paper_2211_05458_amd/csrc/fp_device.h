@@ -493,33 +493,35 @@ __device__ inline int bgm_locate(const MeshView& m, const double* x, double* xi,
 // (kInterpVars).
 // ---------------------------------------------------------------------------
 
+// FP64, in the order of the element kernel's matrix products
+// (interp_f64_mfma): s_q = sum_i U_qi l_i(xi1) as a chain of fused
+// multiply-adds, then s_q l_j(xi2) l_k(xi3), q = k n + j, in four sums by q % 4.
 template <int NN, typename UT>
 __device__ __forceinline__ void interp(const MeshView& m, const UT* __restrict__ U, const double* xi, double* out) {
   double l1[NN], l2[NN];
   lagrange<NN, double>(m.xdg, m.cdg, xi[0], l1);
   lagrange<NN, double>(m.xdg, m.cdg, xi[1], l2);
   constexpr int N3 = NN * NN * NN;
-  double acc[kInterpVars] = {};
-  // one xi3-slab per iteration: the NN*NN nodes of every variable read
+  static_assert(NN % 2 == 0, "two slabs hold a multiple of four rows");
+  double acc[kInterpVars][4] = {};
+  // two xi3-slabs per iteration: the NN*NN nodes of every variable read
 #pragma unroll 1
-  for (int k = 0; k < NN; ++k) {
-    double l3 = lagrange1<NN, double>(m.xdg, m.cdg, xi[2], k);
+  for (int k = 0; k < NN; k += 2) {
+    const double l3[2] = {lagrange1<NN, double>(m.xdg, m.cdg, xi[2], k), lagrange1<NN, double>(m.xdg, m.cdg, xi[2], k + 1)};
 #pragma unroll
     for (int var = 0; var < kInterpVars; ++var) {
       const UT* Uk = U + var * N3 + k * NN * NN;
-      double sk = 0.0;
 #pragma unroll
-      for (int j = 0; j < NN; ++j) {
-        double sj = 0.0;
+      for (int q = 0; q < 2 * NN; ++q) {
+        double s = (double)Uk[q * NN] * l1[0];
 #pragma unroll
-        for (int i = 0; i < NN; ++i) sj += (double)Uk[j * NN + i] * l1[i];
-        sk += sj * l2[j];
+        for (int i = 1; i < NN; ++i) s = fma((double)Uk[q * NN + i], l1[i], s);
+        acc[var][q & 3] = fma(s, l2[q % NN] * l3[q / NN], acc[var][q & 3]);
       }
-      acc[var] += sk * l3;
     }
   }
 #pragma unroll
-  for (int var = 0; var < kInterpVars; ++var) out[var] = acc[var];
+  for (int var = 0; var < kInterpVars; ++var) out[var] = (acc[var][0] + acc[var][1]) + (acc[var][2] + acc[var][3]);
 }
 
 // FP32 interpolation (mixed precision): FP32 basis and accumulation.

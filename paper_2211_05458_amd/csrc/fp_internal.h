@@ -115,11 +115,19 @@ struct Fluid {
 constexpr int kInterpVars = 4;
 
 // particles per element task after the counting sort: two tasks per
-// wavefront, one per half (32), when the stage is mixed and four elements'
-// geometry nodes and FP32 state fit in 27 KB of LDS (three two-wavefront
-// workgroups per SIMD); one task per wavefront (64) otherwise
-__host__ __device__ constexpr int task_particles(int nn, int ng, bool mixed) {
-  return (mixed && 4 * (ng * ng * ng * 3 * 8 + kInterpVars * nn * nn * nn * 4) <= 27 * 1024) ? 32 : 64;
+// wavefront, one per half (32), where the element data that the stage keeps in
+// LDS leave room for them; one task per wavefront (64) otherwise.  Elements
+// hold about 30 particles, so one per wavefront leaves half of every LDS
+// broadcast and VALU instruction idle.  Mixed: four elements' geometry nodes
+// and FP32 state within 27 KB (three two-wavefront workgroups per SIMD).  FP64:
+// the matrix-core interpolation reads the state from global memory, so only
+// the geometry nodes count (1e6 particles on the 32^3 box, N = 5: 554 us a
+// stage against 577 us with one task per wavefront and the state staged);
+// degree 6 (8.2 KB of nodes) and the extra forces (which interpolate per lane
+// from the staged state) keep 64.
+__host__ __device__ constexpr int task_particles(int nn, int ng, bool mixed, bool forces) {
+  if (!mixed) return (!forces && ng < 7) ? 32 : 64;
+  return 4 * (ng * ng * ng * 3 * 8 + kInterpVars * nn * nn * nn * 4) <= 27 * 1024 ? 32 : 64;
 }
 constexpr int kMinTaskParticles = 32;
 

@@ -16,6 +16,8 @@
 //  k_track       physical-space tracking (Sec. 3.2.3/3.2.4) of the queued
 //                segments: face intersection, hand-off, periodic shift, wall
 //                reflection.
+#include <type_traits>
+
 #include "fp_device.h"
 #include "fp_launch.h"
 
@@ -61,6 +63,24 @@ __device__ __forceinline__ void mixed_update(const float* Uc, const double* x, d
   mixed_lsrk(a, x, v, kx, kv, sp, xe);
 }
 
+// drag (plus gravity) and the low-storage update in FP64 from the interpolated
+// density and momentum
+__device__ __forceinline__ void fp64_update(const double* Uc, const double* x, double* v, double* kx, double* kv,
+                                            double d, const Fluid& fl, const StepParams& sp, double* xe) {
+  const double ir = 1.0 / Uc[0];
+  const double u[3] = {Uc[1] * ir, Uc[2] * ir, Uc[3] * ir};
+  double a[3], fD;
+  drag_accel<double>(sp.drag, Uc[0], u, v, d, fl.mu, fl.rho_p, a, fD);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    a[k] += sp.gravity[k];
+    kx[k] = sp.A * kx[k] + sp.dt * v[k];
+    kv[k] = sp.A * kv[k] + sp.dt * a[k];
+    xe[k] = x[k] + sp.B * kx[k];
+    v[k] = v[k] + sp.B * kv[k];
+  }
+}
+
 // interpolation, drag and the low-storage update for one particle.  FORCES:
 // the extra terms of the equation of motion selected in sp.forces (they need
 // the velocity gradient, hence the element's geometry nodes Xe).
@@ -75,28 +95,22 @@ __device__ __forceinline__ void stage_update(const MeshView& m, const UT* __rest
     map_jac<NG>(m, Xe, xi, xm, Jg);
   }
   if (!MIXED) {
-    double a[3];
     if (FORCES) {
-      double val[kInterpVars], dval[kInterpVars][3], u[3], G[3][3];
+      double a[3], val[kInterpVars], dval[kInterpVars][3], u[3], G[3][3];
       interp_grad<NN, double, UT>(m.xdg, m.cdg, Ue, xi, val, dval);
       velocity_gradient<double>(Jg, val, dval, u, G);
       particle_accel<double>(sp.drag, sp.forces, val[0], u, G, v, d, fl.mu, fl.rho_p, sp.gravity, a, nullptr);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        kx[k] = sp.A * kx[k] + sp.dt * v[k];
+        kv[k] = sp.A * kv[k] + sp.dt * a[k];
+        xe[k] = x[k] + sp.B * kx[k];
+        v[k] = v[k] + sp.B * kv[k];
+      }
     } else {
       double Uc[kInterpVars];
       interp<NN, UT>(m, Ue, xi, Uc);
-      double rho = Uc[0], ir = 1.0 / rho;
-      double u[3] = {Uc[1] * ir, Uc[2] * ir, Uc[3] * ir};
-      double fD;
-      drag_accel<double>(sp.drag, rho, u, v, d, fl.mu, fl.rho_p, a, fD);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] += sp.gravity[k];
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      kx[k] = sp.A * kx[k] + sp.dt * v[k];
-      kv[k] = sp.A * kv[k] + sp.dt * a[k];
-      xe[k] = x[k] + sp.B * kx[k];
-      v[k] = v[k] + sp.B * kv[k];
+      fp64_update(Uc, x, v, kx, kv, d, fl, sp, xe);
     }
   } else {
     float vf[3] = {(float)v[0], (float)v[1], (float)v[2]};
@@ -159,6 +173,89 @@ __device__ __forceinline__ void interp_f32_mfma(const MeshView& m, const float* 
   }
 }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Interpolation of the drag law's variables (FP64) for the particles of a
+// whole wavefront, with the contraction over xi_1 on v_mfma_f64_16x16x4f64:
+// rows R = (var, k, j) of the element's state (operand A, in LDS or global
+// memory), 16 particles as columns (operand B: their l_i(xi_1)).  Register r of
+// lane n + 16 g then holds row 16 T + 4 r + g of particle n; the lane applies
+// l_j(xi_2) l_k(xi_3) and the four lane groups' sums are added.  U0, U1: the
+// state of the elements of lanes 0..31 and 32..63, whose first np0, np1 lanes
+// hold particles.  The bases go between the lanes through buf (48 N doubles of
+// LDS).  Every lane of the wavefront calls it.
+//
+// Per lane from LDS, as the per-lane kernel does it, this contraction read 864
+// broadcast values of 8 bytes for 64 lanes (N = 5: 3500 cycles of a CU's LDS
+// bandwidth per wavefront) and issued as many FMAs with half of the lanes
+// active.  The products' rounding is that of a chain of fused multiply-adds, so
+// the per-lane kernel's interp gives the same bits.  Element stage of 1e6
+// particles on the 32^3 box (N = 5): 609 -> 554 us; 1.6e5 on the 20^3 box 141 ->
+// 116 us; 2e5 on the 16^3 box (N = 3) 88 -> 73 us.  It stays bound by Newton's
+// FP64 issue (about 300 instructions per slab of 25 nodes) and the LDS
+// broadcasts of the geometry nodes.
+template <int NN>
+__device__ __forceinline__ void interp_f64_mfma(const MeshView& m, const double* __restrict__ U0,
+                                                const double* __restrict__ U1, int np0, int np1, const double* xi,
+                                                double* __restrict__ buf, double* out) {
+  constexpr int KS = (NN + 3) / 4, Q4 = NN * NN / 4, TILES = kInterpVars * NN * NN / 16;
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  // 16 particles (one lane group's) at a time
+#pragma unroll 1
+  for (int c = 0; c < 4; ++c) {
+    if (16 * (c & 1) >= (c < 2 ? np0 : np1)) continue;
+    wave_sync();
+    if (g == c) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        double l[NN];
+        lagrange<NN, double>(m.xdg, m.cdg, xi[a], l);
+#pragma unroll
+        for (int i = 0; i < NN; ++i) buf[(a * NN + i) * 16 + n] = l[i];
+      }
+    }
+    wave_sync();
+    // rows and weight addresses are formed anew for each group (held over the
+    // loop they spill)
+    int again = 0;
+    asm volatile("" : "+v"(again));
+    const double* Uc = (c < 2 ? U0 : U1) + (n * NN + g + again);
+    const int gq = g + again;
+    double b[KS], W[Q4], acc[kInterpVars] = {};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) b[s] = 4 * s + g < NN ? buf[(4 * s + g) * 16 + n] : 0.0;
+#pragma unroll
+    for (int q = 0; q < Q4; ++q)
+      W[q] = buf[(NN + (4 * q + gq) % NN) * 16 + n] * buf[(2 * NN + (4 * q + gq) / NN) * 16 + n];
+#pragma unroll
+    for (int T = 0; T < TILES; ++T) {
+      v4d d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const double a = 4 * s + g < NN ? Uc[16 * T * NN + 4 * s] : 0.0;
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[s], d, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int M = 4 * T + r;
+        acc[M / Q4] = fma(d[r], W[M % Q4], acc[M / Q4]);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < kInterpVars; ++v) {
+      double t = acc[v];
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      if (g == c) out[v] = t;
+    }
+  }
+}
+
 struct Queues {
   int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word)
   int32_t* next;      // the next stage's counters
@@ -170,53 +267,64 @@ struct Queues {
 };
 
 // Tasks of up to 64 particles: one per wavefront, four wavefronts per
-// workgroup, four per SIMD (at most 128 VGPRs: the Newton and interpolation
-// loops wait on LDS reads, and the fourth wavefront hides more of that
-// latency than the few spilled registers cost).  Tasks of up to 32 particles
-// (mixed stage, small elements): two per wavefront, one per half, each with
-// its own element in LDS, two wavefronts per workgroup, three per SIMD:
-// elements hold about 30 particles, so one element per wavefront leaves half
-// of every LDS broadcast and VALU instruction idle.  (Two FP64 elements per
-// wavefront leave room for only two wavefronts per SIMD, which measured
-// slower, and so do FP32 elements of N = 7 or N_geo = 6.)
+// workgroup.  Tasks of up to 32 (task_particles): two per wavefront, one per
+// half, each with its own element in LDS, two wavefronts per workgroup.
 constexpr int elem_waves(int tp) { return tp == 64 ? 4 : 2; }
 
-// the element kernel's wavefronts per SIMD: four for tasks of 64 particles
-// (three for two tasks of 32 per wavefront), fewer where the staged element
-// data of a workgroup leave room for fewer workgroups in a CU's 160 KB of LDS.
+// the element's fluid state is staged in LDS for the mixed stage and the extra
+// forces, unless it would not fit four elements per workgroup in 48 KB, or the
+// geometry nodes alone take more than 4 KB (N_geo = 6: with U as well, three
+// workgroups per CU and one wavefront per SIMD)
+template <int NN, int NG, typename UT, bool FORCES>
+constexpr bool elem_stage_u() {
+  constexpr int ng3 = NG * NG * NG, nn3 = NN * NN * NN;
+  return (sizeof(UT) == 4 || FORCES) && ng3 * 3 * 8 + kInterpVars * nn3 * (int)sizeof(UT) <= 12 * 1024 && ng3 * 3 * 8 <= 4096;
+}
+
+// doubles of LDS per element for the geometry nodes; the FP64 interpolation's
+// bases take their place once Newton is done, or (degree 6, whose reach test
+// reads the nodes again) a place of their own
+template <int NN, int NG, bool MIXED, bool FORCES>
+constexpr int elem_geo() {
+  constexpr int geo = NG * NG * NG * 3, bases = (!MIXED && !FORCES) ? 48 * NN : 0;
+  return kReach2<NG> ? geo + bases : (geo > bases ? geo : bases);
+}
+
+// the element kernel's wavefronts per SIMD: four (at most 128 VGPRs: the
+// Newton loop waits on LDS reads, and the fourth wavefront hides more of that
+// latency than the few spilled registers cost), three for two tasks per
+// wavefront (FP64, whose interpolation spills at 128: 788 us against 554 us on
+// the 32^3 box), fewer where the staged element data of a workgroup leave room for
+// fewer workgroups in a CU's 160 KB of LDS.
 // Geometry degree 6 takes three: the degree-6 map and its reach test spill
 // about 250 registers at the 128 of four wavefronts per SIMD, and three with
 // fewer spills measured faster on the annular passage (FP64 10.9 -> 9.8 ms,
 // mixed 8.8 -> 7.4 ms per stage; two: 12.4 and 8.7 ms)
-template <int NN, int NG, typename UT, bool MIXED>
+template <int NN, int NG, typename UT, bool MIXED, bool FORCES>
 constexpr int elem_occupancy() {
-  constexpr int tp = task_particles(NN, NG, MIXED), slots = elem_waves(tp) * (64 / tp);
-  constexpr int ng3 = NG * NG * NG, nn3 = NN * NN * NN;
-  constexpr bool stage_u = ng3 * 3 * 8 + kInterpVars * nn3 * (int)sizeof(UT) <= 12 * 1024 && ng3 * 3 * 8 <= 4096;
-  constexpr int lds = slots * (ng3 * 3 * 8 + (stage_u ? kInterpVars * nn3 * (int)sizeof(UT) : 0)) + 64;
+  constexpr int tp = task_particles(NN, NG, MIXED, FORCES), slots = elem_waves(tp) * (64 / tp);
+  constexpr int lds = slots * (elem_geo<NN, NG, MIXED, FORCES>() * 8 +
+                               (elem_stage_u<NN, NG, UT, FORCES>() ? kInterpVars * NN * NN * NN * (int)sizeof(UT) : 0)) + 64;
   constexpr int by_lds = (160 * 1024 / lds) * elem_waves(tp) / 4;
   constexpr int want = (tp == 64 && NG < 7) ? 4 : 3;
   return by_lds < want ? (by_lds < 1 ? 1 : by_lds) : want;
 }
 
 template <int NN, int NG, typename UT, bool MIXED, bool MLP, bool FORCES>
-__global__ __launch_bounds__(64 * elem_waves(task_particles(NN, NG, MIXED)))
-__attribute__((amdgpu_waves_per_eu(elem_occupancy<NN, NG, UT, MIXED>())))
+__global__ __launch_bounds__(64 * elem_waves(task_particles(NN, NG, MIXED, FORCES)))
+__attribute__((amdgpu_waves_per_eu(elem_occupancy<NN, NG, UT, MIXED, FORCES>())))
 void k_stage_elem(MeshView m, const double* __restrict__ X, const double* __restrict__ XN, const UT* __restrict__ U,
                   const FaceRec* __restrict__ faces, const Task* __restrict__ tasks, const int32_t* __restrict__ ntask,
                   Particles P, Fluid fl, StepParams sp, Queues q, unsigned long long* stats) {
   constexpr int NG3 = NG * NG * NG, NN3 = NN * NN * NN;
-  constexpr int TP = task_particles(NN, NG, MIXED), kElemWaves = elem_waves(TP), PER = 64 / TP;
+  constexpr int TP = task_particles(NN, NG, MIXED, FORCES), kElemWaves = elem_waves(TP), PER = 64 / TP;
   constexpr int SLOTS = kElemWaves * PER;
-  // the task element's geometry nodes and fluid state, staged once per task
+  // the task element's geometry nodes (and fluid state), staged once per task
   // with coalesced vector loads and read as LDS broadcasts by every Newton
-  // iteration and the interpolation; U stays in global memory when both would
-  // not fit four elements per workgroup in 48 KB, or when the geometry nodes
-  // alone take more than 4 KB (N_geo = 6: with U as well, three workgroups per
-  // CU and one wavefront per SIMD)
-  constexpr bool kStageU =
-      NG3 * 3 * 8 + kInterpVars * NN3 * (int)sizeof(UT) <= 12 * 1024 && NG3 * 3 * 8 <= 4096;
-  __shared__ double sX[SLOTS][NG3 * 3];
+  // iteration (and the interpolation)
+  constexpr bool kStageU = elem_stage_u<NN, NG, UT, FORCES>();
+  constexpr bool kMfma64 = !MIXED && !FORCES;
+  __shared__ double sX[SLOTS][elem_geo<NN, NG, MIXED, FORCES>()];
   __shared__ UT sU[SLOTS][kStageU ? kInterpVars * NN3 : 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int half = (TP == 64) ? 0 : lane / TP, tl = lane % TP, slot = w * PER + half;
@@ -241,9 +349,9 @@ void k_stage_elem(MeshView m, const double* __restrict__ X, const double* __rest
     }
   }
   __syncthreads();
-  // the mixed stage interpolates on the matrix cores, all lanes together,
-  // between the location of the lanes' particles and their update (the
-  // element's state from LDS, or from global memory where it is not staged)
+  // the stage interpolates on the matrix cores, all lanes together, between the
+  // location of the lanes' particles and their update (mixed: the element's
+  // state from LDS, or from global memory where it is not staged)
   constexpr bool kMfmaInterp = MIXED && !FORCES;
   bool ok = false;
   int e = 0;
@@ -287,10 +395,18 @@ void k_stage_elem(MeshView m, const double* __restrict__ X, const double* __rest
       }
     }
   }
-  float Uc[kInterpVars];
+  std::conditional_t<MIXED, float, double> Uc[kInterpVars];
   if constexpr (kMfmaInterp) {
     if (wid * PER < nt)
       interp_f32_mfma<NN>(m, kStageU ? (const float*)sU[slot] : (const float*)U + (size_t)e * 5 * NN3, xi, Uc);
+  }
+  if constexpr (kMfma64) {
+    if (wid * PER < nt) {
+      const int ea = __builtin_amdgcn_readlane(t.e, 0), eb = __builtin_amdgcn_readlane(t.e, 32);
+      const int ca = __builtin_amdgcn_readlane(t.cnt, 0), cb = __builtin_amdgcn_readlane(t.cnt, 32);
+      interp_f64_mfma<NN>(m, (const double*)U + (size_t)ea * 5 * NN3, (const double*)U + (size_t)eb * 5 * NN3, ca,
+                          TP == 64 ? ca - 32 : cb, xi, sX[w * PER] + (kReach2<NG> ? NG3 * 3 : 0), Uc);
+    }
   }
   if (ok) {
     const double* Xe = sX[slot];
@@ -300,6 +416,7 @@ void k_stage_elem(MeshView m, const double* __restrict__ X, const double* __rest
     double kv[3] = {P.kv[p], P.kv[cap + p], P.kv[2 * cap + p]};
     double xe[3];
     if constexpr (kMfmaInterp) mixed_update(Uc, x, v, kx, kv, P.d[p], fl, sp, xe);
+    else if constexpr (kMfma64) fp64_update(Uc, x, v, kx, kv, P.d[p], fl, sp, xe);
     else stage_update<NN, NG, UT, MIXED, FORCES>(m, Ue, Xe, xi, x, v, kx, kv, P.d[p], fl, sp, xe);
     const FaceRec* Fe = faces + (size_t)e * 6;
     bool any = false;
@@ -728,7 +845,7 @@ hipError_t launch_dep_force_elem(const MeshView& m, const Particles& P, const Fl
 // the element kernel runs when tasks of its size exist (with the extra forces
 // it has an instantiation of its own, except together with the learned guess)
 bool stage_uses_tasks(const StageLaunch& L) {
-  return L.tasks != nullptr && L.task_tp == task_particles(L.m.n, L.m.ng, L.mixed != 0) &&
+  return L.tasks != nullptr && L.task_tp == task_particles(L.m.n, L.m.ng, L.mixed != 0, L.sp.forces != 0) &&
          (L.sp.forces == 0 || !L.mlp);
 }
 
@@ -746,7 +863,7 @@ static void run_stage(const StageLaunch& L, hipStream_t s) {
   }
   if (stage_uses_tasks(L)) {
     // at most E + cap / tp + 1 tasks, 64 / tp per wavefront
-    constexpr int tp = task_particles(NN, NG, MIXED), nw = elem_waves(tp);
+    const int tp = L.task_tp, nw = elem_waves(tp);
     const int64_t max_tasks = (int64_t)m.E + L.P.cap / tp + 1;
     const int64_t waves = (max_tasks * tp + 63) / 64;
     rec(0);
