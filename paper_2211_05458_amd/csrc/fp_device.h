@@ -1262,15 +1262,12 @@ constexpr double kMaxContraction = 0.95;   // the bounds it is compared with hol
 // iterate (off: its squared distance from the line).  ROOT_NEAR and ROOT_OPEN
 // cut the box to where points of the segment can lie; path: the image
 // (path[0], path[1]) + displacement (path[2], path[3]) of the segment in the
-// face's tangent plane there.  (us, vs), dr: with `local`, no point further
-// than dr from (us, vs) counts; sole is cleared where a root exists that may
-// not be the only one further out.
+// face's tangent plane there.
 template <int NG>
 __device__ __forceinline__ int face_root(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
                                          const double* xs, const double* t, double L, const double* n1,
-                                         const double* n2, bool local, double us, double vs, double dr, double* box,
-                                         double& u, double& v, double& al, double& tn, double& off, bool& sole,
-                                         double* path) {
+                                         const double* n2, double* box, double& u, double& v, double& al, double& tn,
+                                         double& off, double* path) {
   constexpr double kOver = 1.0 + 1e-4;
   double p[3], pu[3], pv[3], prev = 1e300;
   bool last = false;
@@ -1279,11 +1276,8 @@ __device__ __forceinline__ int face_root(const double* __restrict__ cp, const Fa
     face_eval<NG>(cp, u, v, p, pu, pv);
     const double r[3] = {p[0] - xs[0], p[1] - xs[1], p[2] - xs[2]};
     const double bu = fabs(u - box[0]) + box[2] * kOver, bv = fabs(v - box[1]) + box[3] * kOver;
-    const double all = sqrt(bu * bu + bv * bv);
-    double reach = all;
-    if (local) reach = fmin(reach, sqrt((u - us) * (u - us) + (v - vs) * (v - vs)) + dr);
     FaceRange R;
-    const bool some = face_range(X, r, t, L, pu, pv, reach, R);
+    const bool some = face_range(X, r, t, L, pu, pv, sqrt(bu * bu + bv * bv), R);
     double nrm[3];
     cross3(pu, pv, nrm);
     const double P0 = dot3(r, n1), P1 = dot3(r, n2);
@@ -1314,14 +1308,7 @@ __device__ __forceinline__ int face_root(const double* __restrict__ cp, const Fa
     const bool out = fabs(u0 + su) > gu || fabs(v0 + sv) > gv;
     const double kap = root_contraction(F, X, n1, n2, A, R.rho);
     if (regular && kap < kMaxContraction) {
-      if (last) {
-        if (local) {
-          // a root past the first exit, out of the reach bound's range?
-          face_range(X, r, t, L, pu, pv, all, R);
-          if (!(root_contraction(F, X, n1, n2, A, R.rho) < kMaxContraction)) sole = false;
-        }
-        return ROOT_ONE;
-      }
+      if (last) return ROOT_ONE;
       // a root on the segment would lie within kap / (1 - kap) of the step's end
       const double rad = kap / (1.0 - kap) * sqrt(su * su + sv * sv) + 1e-9;
       if (fabs(u0 + su) > rad + box[2] || fabs(v0 + sv) > rad + box[3]) return ROOT_NONE;
@@ -1377,11 +1364,9 @@ constexpr double kPartSize = 1e-4;
 template <int NG, class Root>
 __device__ __forceinline__ void part_roots(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
                                            const double* xs, const double* t, double L, const double* n1,
-                                           const double* n2, bool local, double us, double vs, double dr, double* box,
-                                           double u, double v, Root&& root) {
+                                           const double* n2, double* box, double u, double v, Root&& root) {
   float stk[kPartStack][4];
   int sp = 0, parts = 0;
-  bool sole = true;
   // [a0, a1] x [b0, b1] to the stack, rounded outwards: the parts stay a cover
   auto push = [&](double a0, double a1, double b0, double b1) {
     if (!(a1 > a0) || !(b1 > b0) || sp >= kPartStack) return;
@@ -1395,7 +1380,7 @@ __device__ __forceinline__ void part_roots(const double* __restrict__ cp, const 
   while (true) {
     double al, tn, off, path[4];
     const double was = box[2] * box[3];
-    const int res = face_root<NG>(cp, F, X, xs, t, L, n1, n2, local, us, vs, dr, box, u, v, al, tn, off, sole, path);
+    const int res = face_root<NG>(cp, F, X, xs, t, L, n1, n2, box, u, v, al, tn, off, path);
     ++parts;
     if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, v, tn);
     if (res >= ROOT_NEAR) {
@@ -1868,33 +1853,23 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
         curved = test;
       }
       if constexpr (NG > 2) {
-        double us = 0.0, vs = 0.0, dr = 0.0, n1[3], n2[3], box[4] = {0.0, 0.0, 1.0, 1.0}, path[4];
-        bool local = false, open = false;
+        double n1[3], n2[3], box[4] = {0.0, 0.0, 1.0, 1.0}, path[4];
+        bool open = false;
         if (curved) {
+          double u = 0.0, w = 0.0, al, tn, off;
           if (known && !small) {
-            face_coords(f, xi, us, vs);
-            us = fmin(1.0, fmax(-1.0, us));
-            vs = fmin(1.0, fmax(-1.0, vs));
-            // the crossing of an internal face lies where the path can get to
-            // inside the element (the sampled bound; a crossing it misses is
-            // repaired by the location step)
-            if (F.bc == BC_INTERNAL) {
-              double g0, g1;
-              face_coords(f, m.gxi + (size_t)e * 6, g0, g1);
-              dr = L * sqrt(g0 * g0 + g1 * g1) + 1e-6;
-              local = true;
-            }
+            face_coords(f, xi, u, w);
+            u = fmin(1.0, fmax(-1.0, u));
+            w = fmin(1.0, fmax(-1.0, w));
           }
           ray_planes(t, n1, n2);
-          double u = us, w = vs, al, tn, off;
-          bool alone = true;
           const size_t id = (size_t)ef * 6 + f;
-          const int res = face_root<NG>(m.cp + id * (NG * NG * 3), F, m.fext[id], xs, t, L, n1, n2, local, us, vs, dr,
-                                        box, u, w, al, tn, off, alone, path);
+          const int res = face_root<NG>(m.cp + id * (NG * NG * 3), F, m.fext[id], xs, t, L, n1, n2, box, u, w, al, tn,
+                                        off, path);
           open = res >= ROOT_NEAR;
           if ((res == ROOT_ONE || res == ROOT_NEAR) && fabs(u) <= 1.0 + kUVEps && fabs(w) <= 1.0 + kUVEps &&
               al > amin && al <= amax && sign * tn > 0.0)
-            take(al, u, w, alone && !open);
+            take(al, u, w, !open);
         }
         // open faces, one after the other, by the whole wavefront: first each lane
         // takes one of 8 x 8 parts of the open part; a part that this leaves open
@@ -1917,10 +1892,8 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
           }
 #pragma unroll
           for (int k = 0; k < 4; ++k) cell[k] = lane_value(box[k], src);
-          const double oL = lane_value(L, src), ous = lane_value(us, src), ovs = lane_value(vs, src);
-          const double odr = lane_value(dr, src), omin = lane_value(amin, src), omax = lane_value(amax, src);
+          const double oL = lane_value(L, src), omin = lane_value(amin, src), omax = lane_value(amax, src);
           const double osign = lane_value(sign, src), oref = lane_value(small ? best : 0.0, src);
-          const bool olocal = __builtin_amdgcn_readlane((int)local, src) != 0;
           const bool osmall = MORT && __builtin_amdgcn_readlane((int)small, src) != 0;
           ray_planes(ot, o1, o2);
           double key = 1e300, ka = 0.0, ku = 0.0, kw = 0.0;
@@ -1937,9 +1910,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
           unsigned long long again;
           {
             double u = cell[0], w = cell[1], al, tn, off;
-            bool alone = true;
-            const int res = face_root<NG>(co, Fo, Xo, oxs, ot, oL, o1, o2, olocal, ous, ovs, odr, cell, u, w, al, tn,
-                                          off, alone, cpath);
+            const int res = face_root<NG>(co, Fo, Xo, oxs, ot, oL, o1, o2, cell, u, w, al, tn, off, cpath);
             if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, w, tn);
             // (a root given twice is the same root: the smallest displacement counts)
             bool rest = res >= ROOT_NEAR;
@@ -1959,7 +1930,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             const double am = 0.5 * (a0 + a1);
             const double u = lane_value(cpath[0], c) + am * lane_value(cpath[2], c);
             const double w = lane_value(cpath[1], c) + am * lane_value(cpath[3], c);
-            part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, olocal, ous, ovs, odr, b,
+            part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, b,
                            fmin(b[0] + b[2], fmax(b[0] - b[2], u)), fmin(b[1] + b[3], fmax(b[1] - b[3], w)),
                            [&](double al, double ru, double rw, double tn) { root(a0 + al, ru, rw, tn); });
           }
@@ -1991,7 +1962,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
           const int bc = B.bc;
           const bool bent = NG > 2 && B.type == FACE_CURVED;
           excl = entry = -1;
-          reach = 0x3Fu;
+          reach = 0x3Fu;   // the sampled reach bound drops faces of the first leg only
           known = false;
           if (bc == BC_INTERNAL || bc == BC_PERIODIC) {
             const int ne = B.nbr_elem, nf = B.nbr_face, orient = m.fext[(size_t)e * 6 + bf].orient;
@@ -2088,11 +2059,6 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             mode = DONE;
           }
           xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
-          if (known) {
-            // as for the first leg: internal faces out of reach are dropped
-            const double d[3] = {xe[0] - xs[0], xe[1] - xs[1], xe[2] - xs[2]};
-            reach = reachable_faces(m, e, xi, dot3(d, d)) | boundary_faces(m.faces + (size_t)e * 6);
-          }
         }
       }
     }
