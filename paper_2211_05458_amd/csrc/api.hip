@@ -224,11 +224,11 @@ struct Timed {
   }
 };
 
-// the device counters qcnt: a pair of queue counters per stage (stage i clears
+// the device counters qcnt: each stage's queue counters (stage i clears
 // stage i + 1's, the last one stage 0's, so that every step begins alike), the
 // number of element tasks, the list lengths of the final locate and of the
 // learned guess
-enum { kCntTasks = 10, kCntLocate = 12, kCntGuess = 13 };
+enum { kCntTasks = 5 * kStageCounters, kCntLocate, kCntGuess, kCounters };
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -299,7 +299,7 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   L.mlp_rows = take((size_t)kMlpMaxBatch * kMlpRow * 4);
   size_t pc1 = (size_t)std::max<int64_t>(cap, 1);
   L.tasks = take((E + pc1 / kMinTaskParticles + 2) * task_bytes());
-  L.qcnt = take(64);
+  L.qcnt = take(kCounters * 4);
   L.strag = take(pc1 * 4);
   L.trk_p = take(pc1 * 4);
   L.trk_x = take(pc1 * 3 * 8);
@@ -692,7 +692,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   HIPCHK(c, hipMemsetAsync(b + L.stats, 0, 16 * kStatSlots * 8, s));
   HIPCHK(c, hipMemsetAsync(b + L.mlp_flag, 0, E, s));
   HIPCHK(c, hipMemsetAsync(b + L.sort_count, 0, (E + 1) * 4, s));
-  HIPCHK(c, hipMemsetAsync(b + L.qcnt, 0, 64, s));
+  HIPCHK(c, hipMemsetAsync(b + L.qcnt, 0, kCounters * 4, s));
   MeshView& m = c->mv;
   m = MeshView{};
   m.E = c->E; m.ng = c->ng; m.n = c->n; m.n_geo = c->n_geo;
@@ -761,16 +761,21 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   HIPCHK(c, hipMemsetAsync(c->scratch_i32, 0, 64, s));
   HIPCHK(c, launch_face_setup(m, m.X, (const int32_t*)(b + L.nbr_elem), (const int32_t*)(b + L.nbr_face),
                               (const int8_t*)(b + L.bc), (const double*)(b + L.shift), c->Minv.data(),
-                              (FaceRec*)(b + L.faces), (FaceExt*)(b + L.fext), (double*)(b + L.cp), s));
+                              (FaceRec*)(b + L.faces), (FaceExt*)(b + L.fext), (double*)(b + L.cp),
+                              (int32_t*)(b + L.scratch + 24), s));
   HIPCHK(c, launch_nodes(m, (double*)(b + L.xnode), (double*)(b + L.vol), (double*)(b + L.hE), (double*)(b + L.nbox),
                          (double*)(b + L.gxi), c->scratch_i32, (unsigned long long*)(b + L.scratch + 8), s));
   int32_t bad = 0;
   unsigned long long pad_bits = 0;
   HIPCHK(c, hipMemcpyAsync(&bad, c->scratch_i32, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipMemcpyAsync(&pad_bits, b + L.scratch + 8, 8, hipMemcpyDeviceToHost, s));
+  int32_t hard[2] = {0, 0};
+  HIPCHK(c, hipMemcpyAsync(hard, b + L.scratch + 24, 8, hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
   if (bad) return fail(c, FP_EMESH, "fp_bind_workspace: non-positive Jacobian at " + std::to_string(bad) + " nodes");
   std::memcpy(&c->node_pad, &pad_bits, 8);
+  m.n_hard = hard[0];
+  m.n_fold = hard[1];
   c->dep_pad = (unsigned long long*)(b + L.scratch + 16);
   c->np = 0;
   return FP_OK;
@@ -922,8 +927,8 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
       Lc.tasks = c->tasks_valid ? c->tasks : nullptr;
       Lc.task_tp = c->task_tp;
       Lc.ntask = c->qcnt + kCntTasks;
-      Lc.counters = c->qcnt + 2 * i;
-      Lc.next_counters = c->qcnt + 2 * ((i + 1) % S);
+      Lc.counters = c->qcnt + kStageCounters * i;
+      Lc.next_counters = c->qcnt + kStageCounters * ((i + 1) % S);
       Lc.guess_count = c->qcnt + kCntGuess;
       Lc.strag = c->strag;
       Lc.trk_p = c->trk_p;

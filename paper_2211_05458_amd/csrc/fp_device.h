@@ -845,6 +845,10 @@ __device__ inline void face_setup(const double* __restrict__ Xe, int f, const do
   F.type = (planar && bilin && tw <= tol) ? FACE_PLANAR : (bilin ? FACE_BILINEAR : FACE_CURVED);
 }
 
+template <int NG>
+__device__ __forceinline__ void face_eval(const double* __restrict__ cp, double u, double v, double* p, double* pu,
+                                          double* pv);
+
 // Bounds of a face for face_root (see FaceExt) from its Bernstein control
 // points: the tangents and second derivatives of the patch lie in the convex
 // hulls of the control vectors of its hodographs.
@@ -920,6 +924,17 @@ __device__ inline void face_bounds(const double* __restrict__ cp, const FaceRec&
   X.cn = (float)(1.03 * sqrt(cc[0]) + fl);
   X.c1 = (float)(1.03 * sqrt(cc[1]) + fl);
   X.c2f = (float)(1.03 * sqrt(cc[2]) + fl);
+  // smallest stretch of the face's parameters on a lattice
+  double g2 = 1e300;
+  for (int k = 0; k < 25 && F.type == FACE_CURVED; ++k) {
+    double p[3], pu[3], pv[3];
+    face_eval<NG>(cp, -1.0 + 0.5 * (k % 5), -1.0 + 0.5 * (k / 5), p, pu, pv);
+    const double uu = dot3(pu, pu), uv = dot3(pu, pv), vv = dot3(pv, pv);
+    g2 = fmin(g2, 0.5 * (uu + vv) - sqrt(0.25 * (uu - vv) * (uu - vv) + uv * uv));
+  }
+  X.hard = 0;
+  if (F.type == FACE_CURVED && !(X.inv1e > 0.0f && c2 < kMaxBend * kMaxBend * g2))
+    X.hard = c2 < kFoldBend * kFoldBend * g2 ? 1 : 2;
 }
 
 // how the face parameters of the neighbour across face f of element e follow
@@ -1357,19 +1372,25 @@ __device__ __forceinline__ int face_root(const double* __restrict__ cp, const Fa
 // left open (near-tangential paths, long paths over strongly curved faces),
 // passed to root(al, u, v, t . (pu x pv)): the part is cut, carved around the
 // roots found and halved, down to kPartSize, where the last iterate is taken if
-// it lies on the line to 1e-9 face diameters, and for at most kMaxParts parts.
+// it lies on the line to 1e-9 face diameters.  False if that took more than
+// kMaxParts parts, or kPartStack of them at once.
 constexpr int kPartStack = 32, kMaxParts = 256;
 constexpr double kPartSize = 1e-4;
 
 template <int NG, class Root>
-__device__ __forceinline__ void part_roots(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
+__device__ __forceinline__ bool part_roots(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
                                            const double* xs, const double* t, double L, const double* n1,
                                            const double* n2, double* box, double u, double v, Root&& root) {
   float stk[kPartStack][4];
   int sp = 0, parts = 0;
+  bool whole = true;
   // [a0, a1] x [b0, b1] to the stack, rounded outwards: the parts stay a cover
   auto push = [&](double a0, double a1, double b0, double b1) {
-    if (!(a1 > a0) || !(b1 > b0) || sp >= kPartStack) return;
+    if (!(a1 > a0) || !(b1 > b0)) return;
+    if (sp >= kPartStack) {
+      whole = false;
+      return;
+    }
     stk[sp][0] = (float)(0.5 * (a0 + a1));
     stk[sp][1] = (float)(0.5 * (b0 + b1));
     stk[sp][2] = (float)(0.5 * (a1 - a0)) * (1.0f + 1e-6f) + 1e-7f;
@@ -1385,7 +1406,7 @@ __device__ __forceinline__ void part_roots(const double* __restrict__ cp, const 
     if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, v, tn);
     if (res >= ROOT_NEAR) {
       const double l0 = box[0] - box[2], l1 = box[0] + box[2], m0 = box[1] - box[3], m1 = box[1] + box[3];
-      if (parts >= kMaxParts) break;
+      if (parts >= kMaxParts) return false;
       if (res == ROOT_NEAR) {
         // the box without the square around the root
         const double a0 = fmax(l0, u - off), a1 = fmin(l1, u + off);
@@ -1411,7 +1432,7 @@ __device__ __forceinline__ void part_roots(const double* __restrict__ cp, const 
         }
       }
     }
-    if (sp == 0) break;
+    if (sp == 0) return whole;
     --sp;
 #pragma unroll
     for (int k = 0; k < 4; ++k) box[k] = (double)stk[sp][k];
@@ -1419,6 +1440,10 @@ __device__ __forceinline__ void part_roots(const double* __restrict__ cp, const 
     v = box[1];
   }
 }
+
+constexpr int kClipStack = 16;    // boxes of one face
+constexpr int kClipSteps = 64;    // clipping iterations per face
+constexpr double kClipPad = 1e-10;
 
 // restrict a stride-s list of NG Bezier coefficients to [a, b]
 template <int NG>
@@ -1564,8 +1589,8 @@ __device__ inline bool clip_dir(const double* q, int dir, double amin, double am
   lo = fmax(lo, fmax(a1, a2));
   hi = fmin(hi, fmin(b1, b2));
   if (lo > hi) return false;
-  a = fmax(0.0, lo - 1e-9);
-  b = fmin(1.0, hi + 1e-9);
+  a = fmax(0.0, lo - kClipPad);
+  b = fmin(1.0, hi + kClipPad);
   return true;
 }
 
@@ -1598,91 +1623,6 @@ __device__ __forceinline__ bool outside_band(const double* q, double amin, doubl
   return hi < amin || lo > amax;
 }
 
-// The roots of the segment in the part box (centre and half widths in u, v) of
-// a curved face by Bezier clipping, passed to root(al, u, v, t . (pu x pv)):
-// the projected patch is cut to where its convex hull meets both planes and the
-// displacements of the segment, and halved where a cut removes less than a
-// fifth; boxes in the quadratic regime go to a 2-D Newton.  False if the budget
-// ended first.  It needs no bound on derivatives and so serves the faces of
-// which FaceExt has none that helps (inv1e 0: faces folded or bent by more than
-// their tangents): nine particles on the annular passage meshed with 8 x 4 x 8
-// elements, a step: 500-1300 ms with part_roots, 9-11 ms with this.  Its
-// registers and scratch cost a step elsewhere up to 7 % (32^3 box 2880 -> 3025
-// us), and the passage gains (1e6 particles 8969 -> 8696 us).
-constexpr int kClipStack = 16, kClipSteps = 64;
-
-template <int NG, class Root>
-__device__ __noinline__ bool clip_roots(const double* __restrict__ cp, const FaceRec& F, const double* xs,
-                                        const double* t, double L, const double* n1, const double* n2,
-                                        const double* box, Root&& root) {
-  constexpr double kBoxTol = 1e-7, kNewtonBox = 1e-3, kQuadRatio = 0.25;
-  const double pad = 1e-9 * F.diam;
-  double q[NG * NG * 3], stk[kClipStack][4];
-  const double c0 = 0.5 * (box[0] + 1.0), c1 = 0.5 * (box[1] + 1.0);
-  stk[0][0] = fmax(0.0, c0 - 0.5 * box[2]);
-  stk[0][1] = fmin(1.0, c0 + 0.5 * box[2]);
-  stk[0][2] = fmax(0.0, c1 - 0.5 * box[3]);
-  stk[0][3] = fmin(1.0, c1 + 0.5 * box[3]);
-  int sp = 1, budget = kClipSteps;
-#pragma unroll 1
-  while (sp > 0) {
-    --sp;
-    double u0 = stk[sp][0], u1 = stk[sp][1], v0 = stk[sp][2], v1 = stk[sp][3];
-    if (!(u1 > u0) || !(v1 > v0)) continue;
-    project_face<NG>(cp, xs, t, n1, n2, q);
-    patch_restrict<NG, 3>(q, 0, u0, u1);
-    patch_restrict<NG, 3>(q, 1, v0, v1);
-#pragma unroll 1
-    while (true) {
-      double a, b;
-      if (--budget < 0) return false;
-      if (outside_band<NG>(q, -pad, L + pad) || !clip_dir<NG>(q, 0, -pad, L + pad, a, b)) break;
-      patch_restrict<NG, 3>(q, 0, a, b);
-      double w = u1 - u0;
-      u1 = u0 + b * w;
-      u0 += a * w;
-      const double ru = b - a;
-      if (!clip_dir<NG>(q, 1, -pad, L + pad, a, b)) break;
-      patch_restrict<NG, 3>(q, 1, a, b);
-      w = v1 - v0;
-      v1 = v0 + b * w;
-      v0 += a * w;
-      const double rv = b - a, wu = u1 - u0, wv = v1 - v0;
-      const bool conv = (wu <= kBoxTol && wv <= kBoxTol) ||
-                        (wu <= kNewtonBox && wv <= kNewtonBox && ru <= kQuadRatio && rv <= kQuadRatio);
-      const bool su = ru > 0.8 && wu > kBoxTol, sv = rv > 0.8 && wv > kBoxTol;
-      if (conv) {
-        double u = (u0 + u1) - 1.0, v = (v0 + v1) - 1.0, p[3], pu[3], pv[3], nrm[3];
-#pragma unroll 1
-        for (int it = 0; it < 4; ++it) {
-          face_eval<NG>(cp, u, v, p, pu, pv);
-          const double r[3] = {p[0] - xs[0], p[1] - xs[1], p[2] - xs[2]};
-          const double G0 = dot3(r, n1), G1 = dot3(r, n2);
-          const double a0 = dot3(pu, n1), a1 = dot3(pu, n2), b0 = dot3(pv, n1), b1 = dot3(pv, n2);
-          const double det = a0 * b1 - a1 * b0;
-          if (it == 3 || det == 0.0 || !isfinite(det)) {
-            cross3(pu, pv, nrm);
-            root(dot3(r, t), u, v, dot3(nrm, t));
-            break;
-          }
-          u -= (G0 * b1 - G1 * b0) / det;
-          v -= (a0 * G1 - a1 * G0) / det;
-        }
-        break;
-      }
-      if (su || sv) {
-        if (sp + 2 > kClipStack) return false;
-        const bool cu = su && (!sv || wu >= wv);
-        const double um = 0.5 * (u0 + u1), vm = 0.5 * (v0 + v1);
-        stk[sp][0] = cu ? um : u0; stk[sp][1] = u1; stk[sp][2] = cu ? v0 : vm; stk[sp][3] = v1; ++sp;
-        stk[sp][0] = u0; stk[sp][1] = cu ? um : u1; stk[sp][2] = v0; stk[sp][3] = cu ? v1 : vm; ++sp;
-        break;
-      }
-    }
-  }
-  return true;
-}
-
 // displacements [a0, a1] of the segment's piece that a lane searches: 39 equal
 // pieces of 1/40, then halving towards the start, where the last crossing left
 // a root that a nearly tangential path may have its next one close to
@@ -1708,6 +1648,19 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// wave-aggregated queue append: returns the slot of each predicated lane (-1
+// otherwise); must be reached by every lane of the wave
+__device__ __forceinline__ int wave_push(int32_t* counter, bool pred) {
+  unsigned long long mask = __ballot(pred);
+  if (mask == 0ull) return -1;
+  int lane = threadIdx.x & 63;
+  int leader = __ffsll((long long)mask) - 1;
+  int base = 0;
+  if (lane == leader) base = atomicAdd(counter, (int)__popcll(mask));
+  base = __shfl(base, leader, 64);
+  return pred ? base + (int)__popcll(mask & ((1ull << lane) - 1ull)) : -1;
 }
 
 // Physical-space tracking (Sec. 3.2.3) of the queued straight stage segments
@@ -1737,10 +1690,15 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 // enters).  excl: face just met whose only root that is; entry: non-planar
 // face just met whose root at that point (alpha ~ 0, error growing like
 // 1/sin(incidence)) is ignored below kEntryRel * face diameter.
-template <int NG, bool MORT>
+//
+// DEFER: the mesh has a few faces that face_root does not serve (FaceExt::hard
+// 2).  A segment that meets one, or whose search of some face did not end, goes
+// to the list `later` as it was queued (clip_queue).
+template <int NG, bool MORT, bool DEFER>
 __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t* __restrict__ q_p,
                             const double* __restrict__ q_x, const float* __restrict__ q_s,
-                            const uint8_t* __restrict__ q_m, int64_t nq, int max_cross, int& ncross, int& nhits) {
+                            const uint8_t* __restrict__ q_m, int64_t nq, int32_t* later_count,
+                            int32_t* __restrict__ later, int max_cross, int& ncross, int& nhits) {
   const int64_t cap = P.cap;
   const int lane = threadIdx.x & 63;
   for (int64_t base = (int64_t)blockIdx.x * 64; base < nq; base += (int64_t)gridDim.x * 64) {
@@ -1756,6 +1714,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
     int8_t status = ACTIVE;
     bool known = true;    // xi: the leg start's reference coordinates
     bool sole = false;    // the best face has no other root on the segment
+    bool defer = false;
     // mort: the small faces of a big mortar face just crossed (Sec. 3.2.3) are
     // searched for the root nearest that crossing where the path enters the
     // small element
@@ -1776,7 +1735,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
       if (mode == NEW_LEG) {
         t[0] = xe[0] - xs[0]; t[1] = xe[1] - xs[1]; t[2] = xe[2] - xs[2];
         L = sqrt(dot3(t, t));
-        if (L == 0.0) {
+        if (!(L > 0.0 && L < INFINITY)) {   // no path (a displacement that is not finite crosses nothing)
           mode = DONE;
         } else {
           const double iL = 1.0 / L;
@@ -1792,7 +1751,11 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
           mode = FACES;
 #pragma unroll 1
           for (int f = 0; f < 6; ++f)
-            if (f != excl && ((reach >> f) & 1u) && bbox_hit(m.faces[(size_t)e * 6 + f], xs, xe)) todo |= 1u << f;
+            if (f != excl && ((reach >> f) & 1u) && bbox_hit(m.faces[(size_t)e * 6 + f], xs, xe)) {
+              todo |= 1u << f;
+              if (DEFER) defer = defer || m.fext[(size_t)e * 6 + f].hard > 1;
+            }
+          if (DEFER && defer) mode = DONE;
         }
       }
       // the lane's next face: element ef, local face f
@@ -1808,6 +1771,11 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
               ef = se;
               f = sf;
             }
+          }
+          if (DEFER && ef >= 0 && m.fext[(size_t)ef * 6 + f].hard > 1) {
+            defer = true;
+            mode = DONE;
+            ef = -1;
           }
         } else if (todo) {
           ef = e;
@@ -1913,10 +1881,9 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             const int res = face_root<NG>(co, Fo, Xo, oxs, ot, oL, o1, o2, cell, u, w, al, tn, off, cpath);
             if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, w, tn);
             // (a root given twice is the same root: the smallest displacement counts)
-            bool rest = res >= ROOT_NEAR;
-            if (rest && !(Xo.inv1e > 0.0f)) rest = !clip_roots<NG>(co, Fo, oxs, ot, oL, o1, o2, cell, root);
-            again = __ballot(rest);
+            again = __ballot(res >= ROOT_NEAR);
           }
+          bool whole = true;
 #pragma unroll 1
           while (again) {
             const int c = __ffsll((long long)again) - 1;
@@ -1930,9 +1897,15 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             const double am = 0.5 * (a0 + a1);
             const double u = lane_value(cpath[0], c) + am * lane_value(cpath[2], c);
             const double w = lane_value(cpath[1], c) + am * lane_value(cpath[3], c);
-            part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, b,
-                           fmin(b[0] + b[2], fmax(b[0] - b[2], u)), fmin(b[1] + b[3], fmax(b[1] - b[3], w)),
-                           [&](double al, double ru, double rw, double tn) { root(a0 + al, ru, rw, tn); });
+            const bool all =
+                part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, b, fmin(b[0] + b[2], fmax(b[0] - b[2], u)),
+                               fmin(b[1] + b[3], fmax(b[1] - b[3], w)),
+                               [&](double al, double ru, double rw, double tn) { root(a0 + al, ru, rw, tn); });
+            whole = whole && all;
+          }
+          if (DEFER && __ballot(!whole) != 0ull && lane == src) {
+            defer = true;
+            mode = DONE;
           }
           double low = key;
 #pragma unroll
@@ -2062,6 +2035,13 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
         }
       }
     }
+    if (DEFER) {
+      const int at = wave_push(later_count, defer);
+      if (defer) {
+        later[at] = (int32_t)i;
+        continue;
+      }
+    }
     ncross += nseg;
     nhits += hits;
     if (nseg || status != ACTIVE) {
@@ -2082,17 +2062,395 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
   }
 }
 
-// wave-aggregated queue append: returns the slot of each predicated lane (-1
-// otherwise); must be reached by every lane of the wave
-__device__ __forceinline__ int wave_push(int32_t* counter, bool pred) {
-  unsigned long long mask = __ballot(pred);
-  if (mask == 0ull) return -1;
-  int lane = threadIdx.x & 63;
-  int leader = __ffsll((long long)mask) - 1;
-  int base = 0;
-  if (lane == leader) base = atomicAdd(counter, (int)__popcll(mask));
-  base = __shfl(base, leader, 64);
-  return pred ? base + (int)__popcll(mask & ((1ull << lane) - 1ull)) : -1;
+// The same by Bezier clipping (Sec. 3.2.4) on every curved face, for the
+// segments of `list` (null: the whole queue): it needs no bound on derivatives
+// and so serves the faces that face_root does not (FaceExt::hard, kHardShare).
+//
+// Written as a per-lane state machine: one loop iteration advances a lane by
+// one step of its own work (next candidate face, pop of a clipping box, one
+// clipping iteration, end of a leg), so the lanes of a wavefront that test
+// different faces, need different iteration counts or cross different numbers
+// of faces all share the clipping iteration that dominates the cost.  A lane
+// whose segment is done takes the next one from the queue (one atomic per
+// wavefront and iteration for all its idle lanes), so the lanes stay busy until
+// the queue is drained.  The results do not depend on the order.  A search ends
+// after kClipSteps iterations (a path that runs along the face).
+//
+// A kernel of its own: the projected patch and the box stack inside track_queue
+// cost meshes that never use them up to 7 % of a step.
+__device__ __forceinline__ int lane_rank64(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+template <int NG, bool MORT>
+__device__ void clip_queue(const MeshView& m, const Particles& P, const int32_t* __restrict__ list,
+                           const int32_t* __restrict__ q_p, const double* __restrict__ q_x,
+                           const uint8_t* __restrict__ q_m, int32_t* head, int64_t nq, int max_cross, int& ncross,
+                           int& nhits) {
+  constexpr double kBoxTol = 1e-7;
+  // Bezier clipping contracts a box around a simple root quadratically; once
+  // both sides are below kNewtonBox and the last iteration cut each of them to
+  // at most kQuadRatio, the box holds one transversal root and the 2-D Newton
+  // below reaches it in three steps (a double root, where the clipping only
+  // contracts linearly, keeps clipping down to kBoxTol)
+  constexpr double kNewtonBox = 1e-3, kQuadRatio = 0.25;
+  enum { NEW_LEG, NEXT_FACE, POP, CLIP, LEG_END, MORT_FACE, MORT_END, DONE };
+  // idle lanes take new segments once at least kRefill of them wait (one
+  // atomic on the queue head and one pass of the refill code per batch):
+  // measured per-stage tracking, degree 4 with 1.1e6 segments 6.6 -> 5.2 ms
+  // at 32 (8: 6.3, 16: 5.6), degree 6 with 1.3e6 segments 23.7 -> 22.7 ms at
+  // 8 (16: 22.9, 32: 23.8); a queue of 4e4 segments loses 0.01 ms at either
+  constexpr int kRefill = NG >= 7 ? 8 : 32;
+  const int64_t cap = P.cap;
+  // the lane's segment: particle, element at the start, wall hits, crossings
+  int64_t p = -1;
+  int e = 0, e0 = 0, hits = 0, nseg = 0;
+  int8_t status = ACTIVE;
+  unsigned reach = 0x3Fu;
+  double xe[3] = {0, 0, 0}, v[3] = {0, 0, 0}, kx[3] = {0, 0, 0}, kv[3] = {0, 0, 0};
+  double xs[3] = {0, 0, 0};
+  // excl: planar face just entered through (no further root possible);
+  // entry: non-planar face just entered through, whose root at the entry point
+  // (alpha ~ 0, error growing like 1/sin(incidence)) is ignored below
+  // kEntryRel * face diameter
+  int excl = -1, entry = -1, count = 0;
+  double t[3] = {0, 0, 0}, n1[3] = {0, 0, 0}, n2[3] = {0, 0, 0}, L = 0.0, eps = 0.0;
+  double best = 1e300, bu = 0.0, bv = 0.0, amin = 0.0, bmin = 0.0, bmax = 0.0;
+  int bf = -1, f = 0;
+  int fl = 0;   // local index of the face under test (its outward-normal sign)
+  // non-conforming side: mortar index, cursor over its small faces, the
+  // big-face crossing and the small-face root nearest it
+  int mort = -1, mj = 0, mbig = -1, ms = -1, mf = -1, mse = -1, msf = -1;
+  double astar = 0.0, mbd = 1e300, msa = 0.0;
+  const double* cpf = m.cp;
+  double stk[kClipStack][4];
+  int sp = 0, budget = 0;
+  double u0 = 0.0, u1 = 1.0, v0 = 0.0, v1 = 1.0;
+  double q[NG * NG * 3];
+  // a root counts if it lies in (amin, L], on the face, and the path leaves
+  // the element there: tn = t . outward normal > 0 (a root where the path
+  // enters, at a tangential touch or the entry point, is not a crossing)
+  auto consider = [&](double a, double uu, double vv, double tn) {
+    if (fabs(uu) > 1.0 + kUVEps || fabs(vv) > 1.0 + kUVEps) return;
+    if (MORT && mort >= 0) {
+      // small face of a mortar: a root where the path enters the small element
+      // (where the inverted path leaves it), the one nearest the big-face crossing
+      if (!(a >= bmin && a <= bmax) || !(tn < 0.0)) return;
+      const double dd = fabs(a - astar);
+      if (dd < mbd) { mbd = dd; msa = a; mse = ms; msf = mf; }
+      return;
+    }
+    if (!(a > amin && a <= L)) return;
+    if (!(tn > 0.0)) return;
+    if (a < best) { best = a; bf = f; bu = uu; bv = vv; }
+  };
+  int mode = DONE;
+  bool drained = nq == 0;   // wave-uniform: the queue has no segment left
+  const int lane = threadIdx.x & 63;
+#pragma unroll 1
+  while (true) {
+    if (!drained) {
+      const unsigned long long idle = __ballot(mode == DONE);
+      if (idle && (__popcll(idle) >= kRefill || __popcll(idle) == 64)) {
+        const int nidle = __popcll(idle);
+        const int leader = __ffsll((long long)idle) - 1;
+        int base = 0;
+        if (lane == leader) base = atomicAdd(head, nidle);
+        base = __shfl(base, leader, 64);
+        if ((int64_t)base + nidle >= nq) drained = true;
+        if (mode == DONE) {
+          const int64_t at = (int64_t)base + lane_rank64(idle);
+          if (at < nq) {
+            const int64_t i = list ? list[at] : at;
+            p = q_p[i];
+            xs[0] = q_x[i]; xs[1] = q_x[cap + i]; xs[2] = q_x[2 * cap + i];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              xe[k] = P.x[k * cap + p];
+              v[k] = P.v[k * cap + p];
+              kx[k] = P.kx[k * cap + p];
+              kv[k] = P.kv[k * cap + p];
+            }
+            e = e0 = P.elem[p];
+            hits = nseg = 0;
+            status = ACTIVE;
+            reach = q_m[i];
+            excl = entry = -1;
+            count = 0;
+            mort = -1;
+            mode = NEW_LEG;
+          }
+        }
+      }
+    }
+    if (__ballot(mode != DONE) == 0ull) break;
+    if (mode == NEW_LEG) {
+      t[0] = xe[0] - xs[0]; t[1] = xe[1] - xs[1]; t[2] = xe[2] - xs[2];
+      L = sqrt(dot3(t, t));
+      if (L == 0.0) {
+        mode = DONE;
+      } else {
+        double iL = 1.0 / L;
+        t[0] *= iL; t[1] *= iL; t[2] *= iL;
+        ray_planes(t, n1, n2);
+        eps = 1e-12 * m.hE[e];
+        best = 1e300;
+        bf = -1;
+        f = 0;
+        mode = NEXT_FACE;
+      }
+    }
+    if (mode == NEXT_FACE) {
+      // reach: the faces the first leg can reach (all of them on later legs)
+      while (f < 6 && (f == excl || !((reach >> f) & 1u) || !bbox_hit(m.faces[e * 6 + f], xs, xe))) f++;
+      if (f == 6) {
+        mode = LEG_END;
+      } else {
+        const FaceRec& F = m.faces[e * 6 + f];
+        fl = f;
+        amin = (f == entry) ? fmax(eps, kEntryRel * F.diam) : eps;
+        if (F.type != FACE_CURVED) {
+          double al[2], uv[4];
+          int nr = (F.type == FACE_PLANAR) ? planar_hit(F, xs, t, al, uv) : bilinear_hit(F, xs, t, al, uv);
+          for (int r = 0; r < nr; ++r) {
+            double pu[3], pv[3], nrm[3];
+            for (int k = 0; k < 3; ++k) {
+              pu[k] = F.A[k] * uv[2 * r + 1] + F.B[k];
+              pv[k] = F.A[k] * uv[2 * r] + F.C[k];
+            }
+            cross3(pu, pv, nrm);
+            consider(al[r], uv[2 * r], uv[2 * r + 1], kFaceSign[f] * dot3(nrm, t));
+          }
+          f++;
+        } else {
+          // only roots with displacement in (amin, L] matter: clip to a padded band
+          const double pad = 1e-9 * F.diam;
+          bmin = amin - pad;
+          bmax = L + pad;
+          cpf = m.cp + (size_t)(e * 6 + f) * (NG * NG * 3);
+          stk[0][0] = 0.0; stk[0][1] = 1.0; stk[0][2] = 0.0; stk[0][3] = 1.0;
+          sp = 1;
+          budget = kClipSteps;
+          mode = POP;
+        }
+      }
+    }
+    if (MORT && mode == MORT_FACE) {
+      // the small faces of the big mortar face just crossed (Sec. 3.2.3)
+      while (mj < 4 && (m.mortar[mort * 8 + 2 * mj] < 0 ||
+                        !bbox_hit(m.faces[m.mortar[mort * 8 + 2 * mj] * 6 + m.mortar[mort * 8 + 2 * mj + 1]], xs, xe)))
+        mj++;
+      if (mj == 4) {
+        mode = MORT_END;
+      } else {
+        ms = m.mortar[mort * 8 + 2 * mj];
+        mf = m.mortar[mort * 8 + 2 * mj + 1];
+        fl = mf;
+        const FaceRec& F = m.faces[ms * 6 + mf];
+        const double pad = 1e-9 * F.diam;
+        bmin = -pad;
+        bmax = L + pad;
+        if (F.type != FACE_CURVED) {
+          double al[2], uv[4];
+          int nr = (F.type == FACE_PLANAR) ? planar_hit(F, xs, t, al, uv) : bilinear_hit(F, xs, t, al, uv);
+          for (int r = 0; r < nr; ++r) {
+            double pu[3], pv[3], nrm[3];
+            for (int k = 0; k < 3; ++k) {
+              pu[k] = F.A[k] * uv[2 * r + 1] + F.B[k];
+              pv[k] = F.A[k] * uv[2 * r] + F.C[k];
+            }
+            cross3(pu, pv, nrm);
+            consider(al[r], uv[2 * r], uv[2 * r + 1], kFaceSign[mf] * dot3(nrm, t));
+          }
+          mj++;
+        } else {
+          cpf = m.cp + (size_t)(ms * 6 + mf) * (NG * NG * 3);
+          stk[0][0] = 0.0; stk[0][1] = 1.0; stk[0][2] = 0.0; stk[0][3] = 1.0;
+          sp = 1;
+          budget = kClipSteps;
+          mode = POP;
+        }
+      }
+    }
+    if (mode == POP) {
+      if (sp == 0 || budget <= 0) {
+        if (MORT && mort >= 0) {
+          mj++;
+          mode = MORT_FACE;
+        } else {
+          f++;
+          mode = NEXT_FACE;
+        }
+      } else {
+        --sp;
+        u0 = stk[sp][0]; u1 = stk[sp][1]; v0 = stk[sp][2]; v1 = stk[sp][3];
+        project_face<NG>(cpf, xs, t, n1, n2, q);
+        if (u0 != 0.0 || u1 != 1.0) patch_restrict<NG, 3>(q, 0, u0, u1);
+        if (v0 != 0.0 || v1 != 1.0) patch_restrict<NG, 3>(q, 1, v0, v1);
+        mode = CLIP;
+      }
+    }
+    if (mode == CLIP) {
+      // one Bezier-clipping iteration (Sec. 3.2.4) on the live box
+      double a, b;
+      mode = POP;
+      if (--budget >= 0 && !outside_band<NG>(q, bmin, bmax) && clip_dir<NG>(q, 0, bmin, bmax, a, b)) {
+        patch_restrict<NG, 3>(q, 0, a, b);
+        double w = u1 - u0;
+        double nu0 = u0 + a * w, nu1 = u0 + b * w;
+        u0 = nu0; u1 = nu1;
+        const double ru = b - a;
+        if (clip_dir<NG>(q, 1, bmin, bmax, a, b)) {
+          patch_restrict<NG, 3>(q, 1, a, b);
+          w = v1 - v0;
+          double nv0 = v0 + a * w, nv1 = v0 + b * w;
+          v0 = nv0; v1 = nv1;
+          const double rv = b - a;
+          const double wu = u1 - u0, wv = v1 - v0;
+          bool conv = (wu <= kBoxTol && wv <= kBoxTol) ||
+                      (wu <= kNewtonBox && wv <= kNewtonBox && ru <= kQuadRatio && rv <= kQuadRatio);
+          const bool su = (ru > 0.8 && wu > kBoxTol), sv = (rv > 0.8 && wv > kBoxTol);
+          if (!conv && (su || sv) && sp + 2 > kClipStack) conv = true;
+          if (conv) {
+            // 2-D Newton on the plane distances from the box centre
+            double u = (u0 + u1) - 1.0, vv = (v0 + v1) - 1.0;
+            double pp[3], pu[3], pv[3];
+#pragma unroll 1
+            for (int it = 0; it < 3; ++it) {
+              face_eval<NG>(cpf, u, vv, pp, pu, pv);
+              double r[3] = {pp[0] - xs[0], pp[1] - xs[1], pp[2] - xs[2]};
+              double G0 = dot3(r, n1), G1 = dot3(r, n2);
+              double Gu0 = dot3(pu, n1), Gu1 = dot3(pu, n2), Gv0 = dot3(pv, n1), Gv1 = dot3(pv, n2);
+              double det = Gu0 * Gv1 - Gu1 * Gv0;
+              if (det == 0.0 || !isfinite(det)) break;
+              u += -(G0 * Gv1 - G1 * Gv0) / det;
+              vv += -(Gu0 * G1 - Gu1 * G0) / det;
+            }
+            face_eval<NG>(cpf, u, vv, pp, pu, pv);
+            double r3[3] = {pp[0] - xs[0], pp[1] - xs[1], pp[2] - xs[2]}, nrm[3];
+            cross3(pu, pv, nrm);
+            consider(dot3(r3, t), u, vv, kFaceSign[fl] * dot3(nrm, t));
+          } else if (su || sv) {
+            const int dir = (su && sv) ? (wu >= wv ? 0 : 1) : (su ? 0 : 1);
+            if (dir == 0) {
+              const double um = 0.5 * (u0 + u1);
+              stk[sp][0] = um; stk[sp][1] = u1; stk[sp][2] = v0; stk[sp][3] = v1; sp++;
+              stk[sp][0] = u0; stk[sp][1] = um; stk[sp][2] = v0; stk[sp][3] = v1; sp++;
+            } else {
+              const double vm = 0.5 * (v0 + v1);
+              stk[sp][0] = u0; stk[sp][1] = u1; stk[sp][2] = vm; stk[sp][3] = v1; sp++;
+              stk[sp][0] = u0; stk[sp][1] = u1; stk[sp][2] = v0; stk[sp][3] = vm; sp++;
+            }
+          } else {
+            mode = CLIP;   // the box shrank: clip it again
+          }
+        }
+      }
+    }
+    if (mode == LEG_END) {
+      if (bf < 0) {
+        mode = DONE;
+      } else if (count >= max_cross) {
+        status = MAX_CROSS;
+        mode = DONE;
+      } else {
+        count++;
+        nseg++;
+        double xh[3] = {xs[0] + best * t[0], xs[1] + best * t[1], xs[2] + best * t[2]};
+        const int fid = e * 6 + bf;
+        const FaceRec& F = m.faces[fid];
+        const int bc = F.bc;
+        mode = NEW_LEG;
+        reach = 0x3Fu;
+        if (bc == BC_INTERNAL || bc == BC_PERIODIC) {
+          const int ne = F.nbr_elem, nf = F.nbr_face;
+          if (bc == BC_PERIODIC)
+            for (int k = 0; k < 3; ++k) { xh[k] += F.shift[k]; xe[k] += F.shift[k]; }
+          e = ne;
+          const bool planar = m.faces[ne * 6 + nf].type == FACE_PLANAR;
+          excl = planar ? nf : -1;
+          entry = planar ? -1 : nf;
+          xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
+        } else if (MORT && bc == BC_MORTAR) {
+          // non-conforming side: find the small face the path enters through
+          mort = F.nbr_elem;
+          mj = 0;
+          mse = -1;
+          mbd = 1e300;
+          astar = best;
+          mbig = bf;
+          mode = MORT_FACE;
+        } else if (bc == BC_REFLECT) {
+          double nrm[3];
+          if (F.type == FACE_CURVED) {
+            double pp[3], pu[3], pv[3];
+            face_eval<NG>(m.cp + (size_t)fid * (NG * NG * 3), bu, bv, pp, pu, pv);
+            cross3(pu, pv, nrm);
+          } else {
+            double pu[3], pv[3];
+            for (int k = 0; k < 3; ++k) { pu[k] = F.A[k] * bv + F.B[k]; pv[k] = F.A[k] * bu + F.C[k]; }
+            cross3(pu, pv, nrm);
+          }
+          const double il = 1.0 / sqrt(dot3(nrm, nrm));
+          nrm[0] *= il; nrm[1] *= il; nrm[2] *= il;
+          const double r[3] = {xe[0] - xh[0], xe[1] - xh[1], xe[2] - xh[2]};
+          const double dr = dot3(r, nrm), dv = dot3(v, nrm), dkx = dot3(kx, nrm), dkv = dot3(kv, nrm);
+          for (int k = 0; k < 3; ++k) {
+            xe[k] = xh[k] + (r[k] - 2.0 * dr * nrm[k]);
+            v[k] -= 2.0 * dv * nrm[k];
+            kx[k] -= 2.0 * dkx * nrm[k];
+            kv[k] -= 2.0 * dkv * nrm[k];
+          }
+          hits++;
+          excl = (F.type == FACE_PLANAR) ? bf : -1;
+          entry = (F.type == FACE_PLANAR) ? -1 : bf;
+          xs[0] = xh[0]; xs[1] = xh[1]; xs[2] = xh[2];
+        } else {
+          status = OPEN_EXIT;
+          xe[0] = xh[0]; xe[1] = xh[1]; xe[2] = xh[2];
+          mode = DONE;
+        }
+      }
+    }
+    if (MORT && mode == MORT_END) {
+      if (mse >= 0) {
+        // continue from the small-face crossing in the small element
+        e = mse;
+        const bool planar = m.faces[mse * 6 + msf].type == FACE_PLANAR;
+        excl = planar ? msf : -1;
+        entry = planar ? -1 : msf;
+        xs[0] += msa * t[0]; xs[1] += msa * t[1]; xs[2] += msa * t[2];
+      } else {
+        // no small face found (rounding at a seam): the leg ends in the big
+        // element and the next location step finds the particle
+        xs[0] += astar * t[0]; xs[1] += astar * t[1]; xs[2] += astar * t[2];
+        excl = -1;
+        entry = mbig;
+      }
+      mort = -1;
+      mode = NEW_LEG;
+      reach = 0x3Fu;
+    }
+    if (mode == DONE && p >= 0) {
+      // segment done: write back what changed
+      ncross += nseg;
+      nhits += hits;
+      if (nseg || status != ACTIVE) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          P.x[k * cap + p] = xe[k];
+          P.v[k * cap + p] = v[k];
+          P.kx[k * cap + p] = kx[k];
+          P.kv[k * cap + p] = kv[k];
+        }
+        if (e != e0) P.elem[p] = e;
+        if (hits) P.hits[p] += hits;
+        if (status != ACTIVE) P.status[p] = status;
+        P.xi[p] = NAN;   // the continued reference coordinates no longer hold
+      }
+      p = -1;
+    }
+  }
 }
 
 // wave-level sum then one atomic per wave into counter slot blockIdx % 64

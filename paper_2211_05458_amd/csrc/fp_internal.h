@@ -53,10 +53,25 @@ struct FaceRec {
 //   components along the slab frame nrm, e1, e2 of FaceRec.
 // orient: how the neighbour's face parameters follow from this face's (bit 0:
 // swapped, bit 1: first one reversed, bit 2: second one reversed; 8: unknown).
+// hard: 1 for a curved face that these bounds serve badly (kMaxBend, or inv1e
+// 0), 2 for one that they do not serve (kFoldBend).
 struct FaceExt {
   float B[6], inv1e, c2, cn, c1, c2f;
-  int32_t orient;
+  int32_t orient, hard;
 };
+
+// Bound of a face's second derivatives over its smallest tangent from which
+// Newton's search leaves many parts of it open (the passage meshed with 48 x 4 x
+// 48 elements reaches 16, with 40 x 4 x 40 21, with 24 x 4 x 24 55), and from
+// which the search of a few such faces would hold up all others.
+constexpr double kMaxBend = 20.0, kFoldBend = 40.0;
+// The share of hard faces from which a mesh is tracked by clipping alone.
+// Passages with c x 4 x c elements, 5000 particles at ten times the workload's
+// speed, a step by Newton's search and by clipping: c = 32 (11 % hard) 12.3 and
+// 9.8 ms, 36 (9 %) 10.1 and 10.0, 40 (4 %) 8.4 and 10.4, 48 (none) 8.2 and 10.8;
+// 1e5 particles at the workload's speed: 12.1 and 7.0, 8.6 and 7.2, 7.1 and 7.3,
+// 4.9 and 7.7.
+constexpr double kHardShare = 0.05;
 
 // Everything a kernel needs to know about the mesh (passed by value).
 struct MeshView {
@@ -75,6 +90,7 @@ struct MeshView {
   const double* gxi;      // [E][6] upper bounds over the element of |grad xi_i| (0..2) and of the norm of
                           // the Hessian of xi_i (3..5) (sampled, with margins)
   const int32_t* mortar;  // [n_mortar][4][2] (small element, local face) per big mortar face, -1 unused
+  int32_t n_hard, n_fold; // faces with FaceExt::hard > 0, > 1
   int32_t n_mortar;
   double xgeo[kMaxNodes], cgeo[kMaxNodes];  // geometry nodes, 1/prod(x_i - x_j)
   double xdg[kMaxNodes], cdg[kMaxNodes], wdg[kMaxNodes];

@@ -9,7 +9,7 @@ bool supported(int n, int ng);
 
 hipError_t launch_face_setup(const MeshView& m, const double* X, const int32_t* nbr_elem, const int32_t* nbr_face,
                              const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, FaceExt* fext,
-                             double* cp, hipStream_t s);
+                             double* cp, int32_t* n_hard, hipStream_t s);
 hipError_t launch_nodes(const MeshView& m, double* xnode, double* vol, double* hE, double* nbox, double* gxi,
                         int32_t* bad, unsigned long long* node_pad, hipStream_t s);
 hipError_t launch_locate(const MeshView& m, const Particles& P, const int32_t* hint, int64_t n, hipStream_t s);
@@ -18,6 +18,8 @@ hipError_t launch_locate(const MeshView& m, const Particles& P, const int32_t* h
 // and the count of entries that are not positive and finite (*bad, zeroed)
 hipError_t launch_min_positive(const double* d, int64_t n, unsigned long long* inv_bits, int32_t* bad,
                                hipStream_t s);
+constexpr int kStageCounters = 4;   // stragglers, tracking queue, segments to clip, clipping queue's head
+
 struct StageLaunch {
   MeshView m;
   Particles P;
@@ -28,8 +30,8 @@ struct StageLaunch {
   const void* tasks;        // element tasks from the last sort, or null
   int task_tp;              // particles per task of those tasks
   const int32_t* ntask;
-  int32_t* counters;        // queue counters [2], zero at the start
-  int32_t* next_counters;   // [2], left zero for the next stage
+  int32_t* counters;        // queue counters [kStageCounters], zero at the start
+  int32_t* next_counters;   // [kStageCounters], left zero for the next stage
   int32_t* guess_count;     // length of the learned guess's list
   int32_t* strag;           // [cap]
   int32_t* trk_p;           // [cap]

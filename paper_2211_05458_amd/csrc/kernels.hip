@@ -16,7 +16,7 @@ template <int NG>
 __global__ void k_face_setup(int E, const double* __restrict__ X, const int32_t* __restrict__ nbr_elem,
                              const int32_t* __restrict__ nbr_face, const int8_t* __restrict__ bc,
                              const double* __restrict__ shift, MinvArg Mi, FaceRec* faces, FaceExt* fext,
-                             double* cpo) {
+                             double* cpo, int32_t* n_hard) {
   int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= E * 6) return;
   int e = gid / 6, f = gid % 6;
@@ -31,6 +31,8 @@ __global__ void k_face_setup(int E, const double* __restrict__ X, const int32_t*
   face_bounds<NG>(cpo + (size_t)gid * NG * NG * 3, F, B);
   B.orient = (F.bc == BC_INTERNAL || F.bc == BC_PERIODIC) ? face_orientation<NG>(X, e, f, F) : 8;
   fext[gid] = B;
+  if (B.hard > 0) atomicAdd(n_hard, 1);
+  if (B.hard > 1) atomicAdd(n_hard + 1, 1);
 }
 
 // DG node positions x(xi_ijk), volumes w_i w_j w_k J(xi_ijk), element length scale
@@ -373,15 +375,15 @@ static inline dim3 grid_for(int64_t n, int bs = 256) { return dim3((unsigned)((n
 
 hipError_t launch_face_setup(const MeshView& m, const double* X, const int32_t* nbr_elem, const int32_t* nbr_face,
                              const int8_t* bc, const double* shift, const double* Minv, FaceRec* faces, FaceExt* fext,
-                             double* cp, hipStream_t s) {
+                             double* cp, int32_t* n_hard, hipStream_t s) {
   MinvArg Mi;
   for (int i = 0; i < kMaxNodes * kMaxNodes; ++i) Mi.v[i] = (i < m.ng * m.ng) ? Minv[i] : 0.0;
   dim3 g = grid_for((int64_t)m.E * 6, 128);
   switch (m.ng) {
-    case 2: k_face_setup<2><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
-    case 3: k_face_setup<3><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
-    case 5: k_face_setup<5><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
-    case 7: k_face_setup<7><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp); break;
+    case 2: k_face_setup<2><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp, n_hard); break;
+    case 3: k_face_setup<3><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp, n_hard); break;
+    case 5: k_face_setup<5><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp, n_hard); break;
+    case 7: k_face_setup<7><<<g, 128, 0, s>>>(m.E, X, nbr_elem, nbr_face, bc, shift, Mi, faces, fext, cp, n_hard); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

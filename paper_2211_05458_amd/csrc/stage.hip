@@ -257,7 +257,7 @@ __device__ __forceinline__ void interp_f64_mfma(const MeshView& m, const double*
 }
 
 struct Queues {
-  int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word)
+  int32_t* counters;  // [0] stragglers, [1] tracking (one 8-byte aligned word), [2] segments to clip, [3] head of those
   int32_t* next;      // the next stage's counters
   int32_t* strag;     // [cap]
   int32_t* trk_p;     // [cap]
@@ -637,21 +637,36 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
 }
 
 // MORT: the mesh has non-conforming (mortar) faces; conforming meshes run the
-// variant without that part (fewer registers)
-template <int NG, bool MORT>
+// variant without that part (fewer registers).  DEFER: it has faces that Newton's
+// search does not serve; their segments are left to k_track_clip (the straggler
+// list, done with, takes them).
+template <int NG, bool MORT, bool DEFER>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_track(MeshView m, Particles P,
                                                                                       Queues q, StepParams sp,
                                                                                       unsigned long long* stats) {
   int ncross = 0, nhits = 0;
   // the next stage's counters, last read by the stage before this one
-  if (blockIdx.x == 0 && threadIdx.x < 2) q.next[threadIdx.x] = 0;
-  track_queue<NG, MORT>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], sp.max_cross, ncross, nhits);
+  if (blockIdx.x == 0 && threadIdx.x < kStageCounters) q.next[threadIdx.x] = 0;
+  track_queue<NG, MORT, DEFER>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], q.counters + 2, q.strag,
+                               sp.max_cross, ncross, nhits);
+  wave_add(stats + ST_CROSS * kStatSlots, ncross);
+  wave_add(stats + ST_HITS * kStatSlots, nhits);
+}
+
+// ALL: the whole queue instead of the segments that k_track left
+template <int NG, bool MORT, bool ALL>
+__global__ __launch_bounds__(256) void k_track_clip(MeshView m, Particles P, Queues q, StepParams sp,
+                                                    unsigned long long* stats) {
+  int ncross = 0, nhits = 0;
+  if (ALL && blockIdx.x == 0 && threadIdx.x < kStageCounters) q.next[threadIdx.x] = 0;
+  clip_queue<NG, MORT>(m, P, ALL ? nullptr : q.strag, q.trk_p, q.trk_x, q.trk_m, q.counters + 3,
+                       q.counters[ALL ? 1 : 2], sp.max_cross, ncross, nhits);
   wave_add(stats + ST_CROSS * kStatSlots, ncross);
   wave_add(stats + ST_HITS * kStatSlots, nhits);
 }
 
 __global__ void k_reset_counters(int32_t* c) {
-  if (threadIdx.x < 2) c[threadIdx.x] = 0;   // stragglers, tracking queue
+  if (threadIdx.x < 1) c[threadIdx.x] = 0;   // stragglers
 }
 
 // Reference coordinates of the final positions along the element tasks of
@@ -849,6 +864,27 @@ bool stage_uses_tasks(const StageLaunch& L) {
          (L.sp.forces == 0 || !L.mlp);
 }
 
+// Clipping where the mesh has many hard faces (kHardShare), else Newton's search
+// and, for the segments at faces that it does not serve, clipping after it.
+template <int NG, bool MORT>
+static void run_track(const MeshView& m, const Particles& P, int64_t n, const Queues& q, const StepParams& sp,
+                      unsigned long long* stats, hipStream_t s) {
+  const dim3 tg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 63) / 64, 4096)));
+  const dim3 cg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 1024)));
+  if constexpr (NG > 2) {   // faces of degree 1 are never curved
+    if ((double)m.n_hard > kHardShare * 6.0 * m.E) {
+      k_track_clip<NG, MORT, true><<<cg, 256, 0, s>>>(m, P, q, sp, stats);
+      return;
+    }
+    if (m.n_fold > 0) {
+      k_track<NG, MORT, true><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
+      k_track_clip<NG, MORT, false><<<cg, 256, 0, s>>>(m, P, q, sp, stats);
+      return;
+    }
+  }
+  k_track<NG, MORT, false><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
+}
+
 template <int NN, int NG, typename UT, bool MIXED, bool MLP>
 static void run_stage(const StageLaunch& L, hipStream_t s) {
   const MeshView& m = L.m;
@@ -887,10 +923,9 @@ static void run_stage(const StageLaunch& L, hipStream_t s) {
         m, nullptr, L.n, L.P, L.fl, L.sp, q, L.stats);
     rec(3);
   }
-  const dim3 tg((unsigned)std::max<int64_t>(1, std::min<int64_t>((L.n + 63) / 64, 4096)));
   rec(4);
-  if (m.n_mortar > 0) k_track<NG, true><<<tg, 64, 0, s>>>(m, L.P, q, L.sp, L.stats);
-  else k_track<NG, false><<<tg, 64, 0, s>>>(m, L.P, q, L.sp, L.stats);
+  if (m.n_mortar > 0) run_track<NG, true>(m, L.P, L.n, q, L.sp, L.stats, s);
+  else run_track<NG, false>(m, L.P, L.n, q, L.sp, L.stats, s);
   rec(5);
 }
 
