@@ -48,7 +48,7 @@ struct fp_ctx {
   double dl_R = 0.0, dl_per[3] = {0, 0, 0}, dl_pad = 0.0;
   unsigned long long* dep_pad = nullptr;   // largest distance of a particle outside its element box
   float* mlp_rows = nullptr;   // per-row activations for MLP gradients
-  int32_t *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
+  int32_t *tstart = nullptr, *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
   void* tasks = nullptr;
   double* trk_x = nullptr;
   uint8_t* trk_m = nullptr;
@@ -249,7 +249,7 @@ void particle_offsets(int64_t cap, int64_t* off, size_t* total) {
 struct Layout {
   size_t X, faces, fext, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
       mlp_flag, mlp_h1, mlp_ctr, mlp_w, mlp_adam, mlp_order, mlp_bloss, dl_count, dl_start, dl_list, stats,
-      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tasks, qcnt,
+      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tstart, tasks, qcnt,
       strag, trk_p, trk_x, trk_m, trk_s, mlp_guess, part[2], total;
   size_t part_bytes;
 };
@@ -298,6 +298,7 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   L.dep = take((size_t)std::max<int64_t>(cap, 1) * 7 * 8 + 16);
   L.mlp_rows = take((size_t)kMlpMaxBatch * kMlpRow * 4);
   size_t pc1 = (size_t)std::max<int64_t>(cap, 1);
+  L.tstart = take(E * 4);
   L.tasks = take((E + pc1 / kMinTaskParticles + 2) * task_bytes());
   L.qcnt = take(kCounters * 4);
   L.strag = take(pc1 * 4);
@@ -451,7 +452,7 @@ int sort_particles(fp_ctx* c, int tp) {
     return FP_OK;
   }
   HIPCHK(c, launch_sort(c->P[c->cur], c->P[1 - c->cur], c->np, c->E, c->sort_count, c->sort_start, c->sort_rank,
-                        c->sort_sums, tp, c->tasks, c->qcnt + kCntTasks, (int64_t)c->E + c->cap / tp + 2, s));
+                        c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks, (int64_t)c->E + c->cap / tp + 2, s));
   c->cur = 1 - c->cur;
   c->sorts++;
   c->sorted_fresh = true;
@@ -735,6 +736,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   c->scratch_i32 = (int32_t*)(b + L.scratch);
   c->dep_buf = (double*)(b + L.dep);
   c->mlp_rows = (float*)(b + L.mlp_rows);
+  c->tstart = (int32_t*)(b + L.tstart);
   c->tasks = (void*)(b + L.tasks);
   c->qcnt = (int32_t*)(b + L.qcnt);
   c->strag = (int32_t*)(b + L.strag);

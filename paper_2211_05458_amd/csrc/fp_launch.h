@@ -78,8 +78,8 @@ constexpr int kDepListPerElem = 256;   // workspace budget of candidate-list ent
 // counting sort of src into dst and the element tasks of tp particles each;
 // count (E + 1 entries) is zero before and after
 hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count, int32_t* start,
-                       int32_t* rank, int32_t* sums, int tp, void* tasks, int32_t* ntask, int64_t max_tasks,
-                       hipStream_t s);
+                       int32_t* rank, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
+                       int64_t max_tasks, hipStream_t s);
 hipError_t launch_copy_particles(const Particles& S, const Particles& D, int64_t n, hipStream_t s);
 
 // learned guess
