@@ -461,6 +461,23 @@ int sort_particles(fp_ctx* c, int tp) {
   return FP_OK;
 }
 
+// The stages' tasks hold tp particles; those of the last sort may have been cut
+// for another stage kernel (precision, extra forces) or by the source.  The rows
+// still lie as the sort left them.  Uncut, the stages run per lane, which is the
+// faster way for few particles (one launch, no short list of stragglers): FP64
+// steps with and without forces in turn, sorted every fourth step, us a step per
+// lane and recut: 60 000 particles in 12^3 elements 659 and 985, 150 000 in 16^3
+// 1278 and 1251, 200 000 in a straight 20^3 cube 778 and 868, 500 000 in 8^3 1932
+// and 1304, 1e6 in 32^3 6295 and 4689.
+constexpr int64_t kRecutMin = 1 << 18;
+
+int recut_tasks(fp_ctx* c, int tp) {
+  HIPCHK(c, launch_recut(c->E, c->sort_start, c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks,
+                         (int64_t)c->E + c->cap / tp + 2, c->stream));
+  c->task_tp = tp;
+  return FP_OK;
+}
+
 int sync_bound(fp_ctx* c) {
   if (!c->bound || c->cur == 0 || c->np == 0) return FP_OK;
   HIPCHK(c, launch_copy_particles(c->P[1], c->P[0], c->np, c->stream));
@@ -906,6 +923,10 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
         int rc = sort_particles(c, tp);
         if (rc) return rc;
       }
+    } else if (c->tasks_valid && c->task_tp != tp && c->np >= kRecutMin) {
+      Timed tm(c, 0);
+      int rc = recut_tasks(c, tp);
+      if (rc) return rc;
     }
     c->sorted_fresh = false;
     for (int i = 0; i < S; ++i) {

@@ -170,14 +170,25 @@ __device__ __forceinline__ void block_scan2(int& a, int& b, int* ta, int* tb) {
 
 __device__ __forceinline__ int tasks_of(int count, int tp) { return (count + tp - 1) / tp; }
 
+// RECUT: the sort is done, its histogram cleared; a bucket's size from the starts
+// (bucket E is of no interest)
+template <bool RECUT>
+__device__ __forceinline__ int bucket_size(const int32_t* __restrict__ count, const int32_t* __restrict__ start,
+                                           int64_t e, int E) {
+  if (RECUT) return e < E ? start[e + 1] - start[e] : 0;
+  return e <= E ? count[e] : 0;
+}
+
 // sums of each tile of buckets: particles and element tasks (bucket E, the
 // inactive particles, has no tasks)
-__global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ count, int E, int tp, int32_t* sums) {
+template <bool RECUT>
+__global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ count,
+                                                   const int32_t* __restrict__ start, int E, int tp, int32_t* sums) {
   const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
   int a = 0, b = 0, ta, tb;
   for (int k = 0; k < kScanPer; ++k) {
     const int64_t e = b0 + k * 256 + threadIdx.x;
-    const int c = e <= E ? count[e] : 0;
+    const int c = bucket_size<RECUT>(count, start, e, E);
     a += c;
     if (e < E) b += tasks_of(c, tp);
   }
@@ -191,7 +202,8 @@ __global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ c
 // starts of the buckets' particles and of their tasks of at most tp particles,
 // and the number of tasks; the histogram is cleared.  sums: every tile's sums
 // (the workgroup adds those before its own: a few hundred values for the largest
-// meshes).
+// meshes).  RECUT: only the task starts and the number of tasks.
+template <bool RECUT>
 __global__ __launch_bounds__(256) void k_sort_scan(int32_t* __restrict__ count, int32_t* __restrict__ start, int E,
                                                    int tp, const int32_t* __restrict__ sums,
                                                    int32_t* __restrict__ tstart, int32_t* ntask) {
@@ -208,7 +220,7 @@ __global__ __launch_bounds__(256) void k_sort_scan(int32_t* __restrict__ count, 
   int c[kScanPer], a = 0, b = 0;
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
-    c[k] = e0 + k <= E ? count[e0 + k] : 0;
+    c[k] = bucket_size<RECUT>(count, start, e0 + k, E);
     a += c[k];
     if (e0 + k < E) b += tasks_of(c[k], tp);
   }
@@ -219,8 +231,10 @@ __global__ __launch_bounds__(256) void k_sort_scan(int32_t* __restrict__ count, 
   for (int k = 0; k < kScanPer; ++k) {
     const int64_t e = e0 + k;
     if (e > E) break;
-    start[e] = a;
-    count[e] = 0;
+    if (!RECUT) {
+      start[e] = a;
+      count[e] = 0;
+    }
     if (e < E) {
       tstart[e] = b;
       b += tasks_of(c[k], tp);
@@ -237,9 +251,36 @@ hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, in
   if (n == 0) return hipSuccess;
   const dim3 g((unsigned)((n + 255) / 256)), tiles((unsigned)((E + kScanTile) / kScanTile));   // E + 1 buckets
   k_sort_hist<<<g, 256, 0, s>>>(src.status, src.elem, n, E, count, rank);
-  if (tiles.x > 1) k_sort_sums<<<tiles, 256, 0, s>>>(count, E, tp, sums);
-  k_sort_scan<<<tiles, 256, 0, s>>>(count, start, E, tp, sums, tstart, ntask);
+  if (tiles.x > 1) k_sort_sums<false><<<tiles, 256, 0, s>>>(count, start, E, tp, sums);
+  k_sort_scan<false><<<tiles, 256, 0, s>>>(count, start, E, tp, sums, tstart, ntask);
   k_sort_scatter<<<g, 256, 0, s>>>(src, dst, n, E, start, rank, tstart, tp, (Task*)tasks, max_tasks);
+  return hipGetLastError();
+}
+
+// tasks of another size from the bucket starts: each finds its element in the
+// task starts
+__global__ __launch_bounds__(256) void k_task_fill(const int32_t* __restrict__ start,
+                                                   const int32_t* __restrict__ tstart, int E, int tp,
+                                                   const int32_t* __restrict__ ntask, Task* __restrict__ tasks,
+                                                   int64_t max_tasks) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= max_tasks || i >= *ntask) return;
+  int lo = 0, hi = E;   // the last element whose first task is at most i: the only one of them with tasks
+  while (hi - lo > 1) {
+    const int mid = lo + (hi - lo) / 2;
+    if (tstart[mid] <= i) lo = mid;
+    else hi = mid;
+  }
+  const int p0 = start[lo] + ((int)i - tstart[lo]) * tp;
+  tasks[i] = Task{lo, p0, min(tp, start[lo + 1] - p0), 0};
+}
+
+hipError_t launch_recut(int E, int32_t* start, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
+                        int64_t max_tasks, hipStream_t s) {
+  const dim3 tiles((unsigned)((E + kScanTile) / kScanTile)), g((unsigned)((max_tasks + 255) / 256));
+  if (tiles.x > 1) k_sort_sums<true><<<tiles, 256, 0, s>>>(nullptr, start, E, tp, sums);
+  k_sort_scan<true><<<tiles, 256, 0, s>>>(nullptr, start, E, tp, sums, tstart, ntask);
+  k_task_fill<<<g, 256, 0, s>>>(start, tstart, E, tp, ntask, (Task*)tasks, max_tasks);
   return hipGetLastError();
 }
 
