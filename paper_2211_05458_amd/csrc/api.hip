@@ -54,6 +54,7 @@ struct fp_ctx {
   uint8_t* trk_m = nullptr;
   float* trk_s = nullptr;
   bool tasks_valid = false;
+  bool stage_unclean = false, sort_unclean = false;   // a step or sort ended early: its counters may hold values
   // fluid
   Fluid fl{};
   bool fluid_ok = false;
@@ -451,8 +452,13 @@ int sort_particles(fp_ctx* c, int tp) {
     c->tasks_valid = false;
     return FP_OK;
   }
+  // the sort finds its histogram cleared, and leaves it so
+  if (c->sort_unclean) HIPCHK(c, launch_clear_i32(c->sort_count, (int64_t)c->E + 1, s));
+  c->sort_unclean = true;
+  c->tasks_valid = false;
   HIPCHK(c, launch_sort(c->P[c->cur], c->P[1 - c->cur], c->np, c->E, c->sort_count, c->sort_start, c->sort_rank,
                         c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks, (int64_t)c->E + c->cap / tp + 2, s));
+  c->sort_unclean = false;
   c->cur = 1 - c->cur;
   c->sorts++;
   c->sorted_fresh = true;
@@ -472,9 +478,11 @@ int sort_particles(fp_ctx* c, int tp) {
 constexpr int64_t kRecutMin = 1 << 18;
 
 int recut_tasks(fp_ctx* c, int tp) {
+  c->tasks_valid = false;
   HIPCHK(c, launch_recut(c->E, c->sort_start, c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks,
                          (int64_t)c->E + c->cap / tp + 2, c->stream));
   c->task_tp = tp;
+  c->tasks_valid = true;
   return FP_OK;
 }
 
@@ -711,6 +719,7 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   HIPCHK(c, hipMemsetAsync(b + L.mlp_flag, 0, E, s));
   HIPCHK(c, hipMemsetAsync(b + L.sort_count, 0, (E + 1) * 4, s));
   HIPCHK(c, hipMemsetAsync(b + L.qcnt, 0, kCounters * 4, s));
+  c->stage_unclean = c->sort_unclean = false;
   MeshView& m = c->mv;
   m = MeshView{};
   m.E = c->E; m.ng = c->ng; m.n = c->n; m.n_geo = c->n_geo;
@@ -914,6 +923,9 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
   sp.mlp_guess = (sp.use_mlp && c->n_flagged > 0) ? c->mlp_guess : nullptr;
   hipStream_t s = c->stream;
   const int tp = task_particles(c->n, c->ng, o->precision == 1, o->forces != 0);
+  // stage 0 finds its counters cleared by the last step's last stage
+  if (c->stage_unclean) HIPCHK(c, launch_clear_i32(c->qcnt, kCntTasks, s));
+  c->stage_unclean = true;
   for (int st = 0; st < n_steps; ++st) {
     if (o->sort_every < 0 || (o->sort_every > 0 && (c->steps_done % o->sort_every) == 0)) {
       // a sort since the particles last moved (the shape-kernel source sorts
@@ -971,6 +983,7 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
     }
     c->steps_done++;
   }
+  c->stage_unclean = false;
   c->xi_dirty = true;
   c->xi_warm = sp.warm != 0;
   {

@@ -83,6 +83,7 @@ hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, in
 // the last sort's buckets (its starts) cut into tasks of tp particles
 hipError_t launch_recut(int E, int32_t* start, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
                         int64_t max_tasks, hipStream_t s);
+hipError_t launch_clear_i32(int32_t* a, int64_t n, hipStream_t s);
 hipError_t launch_copy_particles(const Particles& S, const Particles& D, int64_t n, hipStream_t s);
 
 // learned guess

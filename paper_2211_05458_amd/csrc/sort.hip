@@ -284,6 +284,16 @@ hipError_t launch_recut(int E, int32_t* start, int32_t* sums, int32_t* tstart, i
   return hipGetLastError();
 }
 
+__global__ void k_clear_i32(int32_t* a, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = 0;
+}
+
+hipError_t launch_clear_i32(int32_t* a, int64_t n, hipStream_t s) {
+  k_clear_i32<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(a, n);
+  return hipGetLastError();
+}
+
 // the first n particles of S to the same rows of D (a caller-owned block)
 __global__ __launch_bounds__(256) void k_copy_particles(Particles S, Particles D, int64_t n) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
