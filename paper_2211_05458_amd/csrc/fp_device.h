@@ -1373,16 +1373,26 @@ __device__ __forceinline__ int face_root(const double* __restrict__ cp, const Fa
 // passed to root(al, u, v, t . (pu x pv)): the part is cut, carved around the
 // roots found and halved, down to kPartSize, where the last iterate is taken if
 // it lies on the line to 1e-9 face diameters.  False if that took more than
-// kMaxParts parts, or kPartStack of them at once.
-constexpr int kPartStack = 32, kMaxParts = 256;
+// `left` parts, which it counts down, or kPartStack of them at once.
+constexpr int kPartStack = 32;
 constexpr double kPartSize = 1e-4;
+// Parts per lane of one face's search, and of the searches that a wavefront makes
+// one after the other per segment that it holds; beyond them, or after one that
+// did not end, the segments of its open faces are left to clip_queue.  A path
+// along a face, within 1e-6 of an element of it, would take thousands of parts:
+// 50 particles along a cylinder's wall, half an element a step, 190 ms without
+// limits, 4.9 ms with them and 1.2 ms by clipping alone; within 1e-4 11.5, 1.2 and
+// 1.2 ms, 1e4 particles within 1e-2 1.1 and 2.1 ms by clipping.  With 40 parts a
+// face long paths on bent faces go to clipping that 64 finish (1e5 particles, 40 x
+// 4 x 40 passage at ten times the speed 21 -> 15 ms a step).
+constexpr int kFaceParts = 64, kSegmentParts = 16;
 
 template <int NG, class Root>
 __device__ __forceinline__ bool part_roots(const double* __restrict__ cp, const FaceRec& F, const FaceExt& X,
                                            const double* xs, const double* t, double L, const double* n1,
-                                           const double* n2, double* box, double u, double v, Root&& root) {
+                                           const double* n2, double* box, double u, double v, int& left, Root&& root) {
   float stk[kPartStack][4];
-  int sp = 0, parts = 0;
+  int sp = 0;
   bool whole = true;
   // [a0, a1] x [b0, b1] to the stack, rounded outwards: the parts stay a cover
   auto push = [&](double a0, double a1, double b0, double b1) {
@@ -1402,11 +1412,11 @@ __device__ __forceinline__ bool part_roots(const double* __restrict__ cp, const 
     double al, tn, off, path[4];
     const double was = box[2] * box[3];
     const int res = face_root<NG>(cp, F, X, xs, t, L, n1, n2, box, u, v, al, tn, off, path);
-    ++parts;
+    --left;
     if (res == ROOT_ONE || res == ROOT_NEAR) root(al, u, v, tn);
     if (res >= ROOT_NEAR) {
       const double l0 = box[0] - box[2], l1 = box[0] + box[2], m0 = box[1] - box[3], m1 = box[1] + box[3];
-      if (parts >= kMaxParts) return false;
+      if (left <= 0) return false;
       if (res == ROOT_NEAR) {
         // the box without the square around the root
         const double a0 = fmax(l0, u - off), a1 = fmin(l1, u + off);
@@ -1685,25 +1695,38 @@ __device__ __forceinline__ int wave_push(int32_t* counter, bool pred) {
 // the evaluation itself) and, on the passage, the wavefronts with the most
 // open faces.
 //
+// The search of open faces is serial in each wavefront, so few segments are
+// spread over more wavefronts than 64 to each would fill: degree 6, where half of
+// the faces stay open, up to 4096 (1e6 particles on the passage 10.0 -> 9.4 ms a
+// step, 2.5e5 mixed 4.6 -> 3.8 ms), degree 2 and 4, where few do, up to 1024 (mortar
+// box of 1e5 1440 -> 1340 us; 4096 would leave the lanes of the large boxes idle:
+// 32^3 of 1e6 particles 2910 -> 3100 us).
+//
 // A root counts if it lies on the face and the path leaves the element there
 // (t . outward normal > 0; at a tangential touch or the entry point the path
 // enters).  excl: face just met whose only root that is; entry: non-planar
 // face just met whose root at that point (alpha ~ 0, error growing like
 // 1/sin(incidence)) is ignored below kEntryRel * face diameter.
 //
-// DEFER: the mesh has a few faces that face_root does not serve (FaceExt::hard
-// 2).  A segment that meets one, or whose search of some face did not end, goes
-// to the list `later` as it was queued (clip_queue).
-template <int NG, bool MORT, bool DEFER>
+// A segment that meets a face that face_root does not serve (FaceExt::hard 2),
+// or whose search of some face does not end within its limits (paths that run
+// along a face), goes to the list `later` as it was queued (clip_queue).
+constexpr int kTrackMin = 4;   // segments of a wavefront
+template <int NG>
+__host__ __device__ constexpr int track_waves() { return NG >= 7 ? 4096 : 1024; }
+
+template <int NG, bool MORT>
 __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t* __restrict__ q_p,
                             const double* __restrict__ q_x, const float* __restrict__ q_s,
                             const uint8_t* __restrict__ q_m, int64_t nq, int32_t* later_count,
                             int32_t* __restrict__ later, int max_cross, int& ncross, int& nhits) {
   const int64_t cap = P.cap;
   const int lane = threadIdx.x & 63;
-  for (int64_t base = (int64_t)blockIdx.x * 64; base < nq; base += (int64_t)gridDim.x * 64) {
+  // few segments are spread over the wavefronts (track_waves)
+  const int per = (int)min((int64_t)64, max((int64_t)kTrackMin, (nq + track_waves<NG>() - 1) / track_waves<NG>()));
+  for (int64_t base = (int64_t)blockIdx.x * per; base < nq; base += (int64_t)gridDim.x * per) {
     const int64_t i = base + lane;
-    const bool have = i < nq;
+    const bool have = lane < per && i < nq;
     const int64_t p = have ? q_p[i] : 0;
     enum { DONE, NEW_LEG, FACES };
     int mode = have ? NEW_LEG : DONE;
@@ -1720,6 +1743,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
     // small element
     int mort = -1, mj = 0, mse = -1, msf = -1;
     double mbd = 1e300, msa = 0.0;
+    int spent = 0;        // the wavefront's searches of open faces, in parts
     if (have) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -1753,9 +1777,9 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
           for (int f = 0; f < 6; ++f)
             if (f != excl && ((reach >> f) & 1u) && bbox_hit(m.faces[(size_t)e * 6 + f], xs, xe)) {
               todo |= 1u << f;
-              if (DEFER) defer = defer || m.fext[(size_t)e * 6 + f].hard > 1;
+              if (NG > 2 && m.n_fold > 0) defer = defer || m.fext[(size_t)e * 6 + f].hard > 1;
             }
-          if (DEFER && defer) mode = DONE;
+          if (defer) mode = DONE;
         }
       }
       // the lane's next face: element ef, local face f
@@ -1772,7 +1796,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
               f = sf;
             }
           }
-          if (DEFER && ef >= 0 && m.fext[(size_t)ef * 6 + f].hard > 1) {
+          if (NG > 2 && m.n_fold > 0 && ef >= 0 && m.fext[(size_t)ef * 6 + f].hard > 1) {
             defer = true;
             mode = DONE;
             ef = -1;
@@ -1840,9 +1864,10 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             take(al, u, w, !open);
         }
         // open faces, one after the other, by the whole wavefront: first each lane
-        // takes one of 8 x 8 parts of the open part; a part that this leaves open
-        // (one in four faces has one: a nearly tangential path) is searched again
-        // with each lane on one piece of the segment, from the piece's image
+        // takes one of 8 x 8 parts of the open part; the box around the parts that
+        // this leaves open (one in four faces has some: a nearly tangential path) is
+        // searched again with each lane on one piece of the segment, from the
+        // piece's image
         unsigned long long left = __ballot(open);
 #pragma unroll 1
         while (left) {
@@ -1883,27 +1908,41 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
             // (a root given twice is the same root: the smallest displacement counts)
             again = __ballot(res >= ROOT_NEAR);
           }
-          bool whole = true;
-#pragma unroll 1
-          while (again) {
-            const int c = __ffsll((long long)again) - 1;
-            again &= again - 1ull;
-            double b[4], a0, a1, ps[3];
+          bool whole = again == 0ull || spent < kSegmentParts * per;
+          if (again && whole) {
+            const bool mine = (again >> lane) & 1ull;
+            double l0 = mine ? cell[0] - cell[2] : 1e300, l1 = mine ? cell[0] + cell[2] : -1e300;
+            double m0 = mine ? cell[1] - cell[3] : 1e300, m1 = mine ? cell[1] + cell[3] : -1e300;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) b[k] = lane_value(cell[k], c);
+            for (int o = 32; o > 0; o >>= 1) {
+              l0 = fmin(l0, __shfl_xor(l0, o, 64));
+              l1 = fmax(l1, __shfl_xor(l1, o, 64));
+              m0 = fmin(m0, __shfl_xor(m0, o, 64));
+              m1 = fmax(m1, __shfl_xor(m1, o, 64));
+            }
+            cell[0] = 0.5 * (l0 + l1);
+            cell[1] = 0.5 * (m0 + m1);
+            cell[2] = 0.5 * (l1 - l0);
+            cell[3] = 0.5 * (m1 - m0);
+            double a0, a1, ps[3];
             segment_piece(lane, oL, a0, a1);
 #pragma unroll
             for (int k = 0; k < 3; ++k) ps[k] = oxs[k] + a0 * ot[k];
             const double am = 0.5 * (a0 + a1);
-            const double u = lane_value(cpath[0], c) + am * lane_value(cpath[2], c);
-            const double w = lane_value(cpath[1], c) + am * lane_value(cpath[3], c);
+            const double u = lane_value(path[0], src) + am * lane_value(path[2], src);
+            const double w = lane_value(path[1], src) + am * lane_value(path[3], src);
+            int parts = kFaceParts;
             const bool all =
-                part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, b, fmin(b[0] + b[2], fmax(b[0] - b[2], u)),
-                               fmin(b[1] + b[3], fmax(b[1] - b[3], w)),
+                part_roots<NG>(co, Fo, Xo, ps, ot, a1 - a0, o1, o2, cell, fmin(l1, fmax(l0, u)),
+                               fmin(m1, fmax(m0, w)), parts,
                                [&](double al, double ru, double rw, double tn) { root(a0 + al, ru, rw, tn); });
-            whole = whole && all;
+            whole = __ballot(!all) == 0ull;
+            int used = kFaceParts - parts;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) used = max(used, __shfl_xor(used, o, 64));
+            spent += whole ? __builtin_amdgcn_readfirstlane(used) : kSegmentParts * per;
           }
-          if (DEFER && __ballot(!whole) != 0ull && lane == src) {
+          if (!whole && lane == src) {
             defer = true;
             mode = DONE;
           }
@@ -2035,7 +2074,7 @@ __device__ void track_queue(const MeshView& m, const Particles& P, const int32_t
         }
       }
     }
-    if (DEFER) {
+    if (NG > 2) {
       const int at = wave_push(later_count, defer);
       if (defer) {
         later[at] = (int32_t)i;

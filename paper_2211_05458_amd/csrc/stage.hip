@@ -637,18 +637,17 @@ __global__ __launch_bounds__(256) void k_stage_lane(MeshView m, const int32_t* _
 }
 
 // MORT: the mesh has non-conforming (mortar) faces; conforming meshes run the
-// variant without that part (fewer registers).  DEFER: it has faces that Newton's
-// search does not serve; their segments are left to k_track_clip (the straggler
-// list, done with, takes them).
-template <int NG, bool MORT, bool DEFER>
+// variant without that part (fewer registers).  The segments that it leaves to
+// k_track_clip go to the straggler list, which is done with.
+template <int NG, bool MORT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_track(MeshView m, Particles P,
                                                                                       Queues q, StepParams sp,
                                                                                       unsigned long long* stats) {
   int ncross = 0, nhits = 0;
   // the next stage's counters, last read by the stage before this one
   if (blockIdx.x == 0 && threadIdx.x < kStageCounters) q.next[threadIdx.x] = 0;
-  track_queue<NG, MORT, DEFER>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], q.counters + 2, q.strag,
-                               sp.max_cross, ncross, nhits);
+  track_queue<NG, MORT>(m, P, q.trk_p, q.trk_x, q.trk_s, q.trk_m, q.counters[1], q.counters + 2, q.strag,
+                        sp.max_cross, ncross, nhits);
   wave_add(stats + ST_CROSS * kStatSlots, ncross);
   wave_add(stats + ST_HITS * kStatSlots, nhits);
 }
@@ -865,24 +864,26 @@ bool stage_uses_tasks(const StageLaunch& L) {
 }
 
 // Clipping where the mesh has many hard faces (kHardShare), else Newton's search
-// and, for the segments at faces that it does not serve, clipping after it.
+// and clipping for what it leaves.  On a mesh without folded faces that is mostly
+// nothing: the launch costs about 2 % of a step of few particles, and one
+// workgroup per CU, what its registers leave room for, is enough.
 template <int NG, bool MORT>
 static void run_track(const MeshView& m, const Particles& P, int64_t n, const Queues& q, const StepParams& sp,
                       unsigned long long* stats, hipStream_t s) {
-  const dim3 tg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 63) / 64, 4096)));
-  const dim3 cg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 1024)));
-  if constexpr (NG > 2) {   // faces of degree 1 are never curved
-    if ((double)m.n_hard > kHardShare * 6.0 * m.E) {
+  const dim3 tg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + kTrackMin - 1) / kTrackMin, 4096)));
+  if constexpr (NG == 2) {   // faces of degree 1 are never curved
+    k_track<NG, MORT><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
+  } else {
+    const bool all = (double)m.n_hard > kHardShare * 6.0 * m.E;
+    const int64_t most = all || m.n_fold > 0 ? 1024 : 256;
+    const dim3 cg((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, most)));
+    if (all) {
       k_track_clip<NG, MORT, true><<<cg, 256, 0, s>>>(m, P, q, sp, stats);
-      return;
-    }
-    if (m.n_fold > 0) {
-      k_track<NG, MORT, true><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
+    } else {
+      k_track<NG, MORT><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
       k_track_clip<NG, MORT, false><<<cg, 256, 0, s>>>(m, P, q, sp, stats);
-      return;
     }
   }
-  k_track<NG, MORT, false><<<tg, 64, 0, s>>>(m, P, q, sp, stats);
 }
 
 template <int NN, int NG, typename UT, bool MIXED, bool MLP>
