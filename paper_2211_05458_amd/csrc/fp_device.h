@@ -1683,17 +1683,16 @@ __device__ __forceinline__ int wave_push(int32_t* counter, bool pred) {
 //
 // Every iteration takes each lane one face further (or to its next leg).  A
 // curved face is one Newton search per lane (face_root); a face that leaves
-// open is searched by the whole wavefront, 64 parts of it at once, which reads
-// that face's data through uniform addresses.  Bezier clipping, which this
-// replaces, held the projected patch (75 doubles for degree 4, 147 for degree
-// 6, spilled) at one wavefront per SIMD and took some 30 long iterations for
-// the slowest lane of a wavefront; a Newton search takes 1 (no crossing) to 4
-// evaluations of the face and needs no patch.  Measured per stage: 1.6e5
-// segments of degree 4 (1e6 particles, 32^3 box) 431 -> 148 us, 3e5 of degree
-// 6 (1e6 particles, annular passage) 3003 -> 1383 us, 1300 segments (4^3 box)
-// 116 -> 32 us.  What is left is the FP64 issue of the bounds (about as long as
-// the evaluation itself) and, on the passage, the wavefronts with the most
-// open faces.
+// open is searched by the whole wavefront, 64 parts of it at once (every lane
+// loads that face's control points).  Clipping (clip_queue) holds the projected
+// patch (75 doubles for degree 4, 147 for degree 6, spilled) at one wavefront per
+// SIMD and takes some 30 long iterations for the slowest lane of a wavefront; a
+// Newton search takes 1 (no crossing) to 4 evaluations of the face and needs no
+// patch.  Measured per stage against clipping everything: 1.6e5 segments of
+// degree 4 (1e6 particles, 32^3 box) 431 -> 158 us, 3e5 of degree 6 (1e6
+// particles, annular passage) 3003 -> 1418 us, 1300 segments (4^3 box) 116 -> 29
+// us.  What is left is the FP64 issue of the bounds (about as long as the
+// evaluation itself) and, on the passage, the wavefronts with the most open faces.
 //
 // The search of open faces is serial in each wavefront, so few segments are
 // spread over more wavefronts than 64 to each would fill: degree 6, where half of

@@ -65,12 +65,13 @@ struct FaceExt {
 // 48 elements reaches 16, with 40 x 4 x 40 21, with 24 x 4 x 24 55), and from
 // which the search of a few such faces would hold up all others.
 constexpr double kMaxBend = 20.0, kFoldBend = 40.0;
-// The share of hard faces from which a mesh is tracked by clipping alone.
-// Passages with c x 4 x c elements, 5000 particles at ten times the workload's
-// speed, a step by Newton's search and by clipping: c = 32 (11 % hard) 12.3 and
-// 9.8 ms, 36 (9 %) 10.1 and 10.0, 40 (4 %) 8.4 and 10.4, 48 (none) 8.2 and 10.8;
-// 1e5 particles at the workload's speed: 12.1 and 7.0, 8.6 and 7.2, 7.1 and 7.3,
-// 4.9 and 7.7.
+// The share of hard faces from which a mesh is tracked by clipping alone: where
+// 1e5 particles at ten times the workload's speed take as long either way.
+// Passages with c x 4 x c elements, those by Newton's search and by clipping, ms a
+// step: c = 32 (11 % hard) 25.4 and 14.3, 36 (9 %) 20.6 and 14.7, 40 (4 %) 15.2 and
+// 14.4, 48 (none) 11.9 and 15.2; 1e5 at the workload's speed 7.2 and 7.0, 5.2 and
+// 7.5, 4.4 and 7.3, 4.1 and 7.7.  (Fewer and slower particles gain by Newton's
+// search up to 11 %: 500 on c = 32 1.8 and 3.1 ms.)
 constexpr double kHardShare = 0.05;
 
 // Everything a kernel needs to know about the mesh (passed by value).
@@ -138,7 +139,9 @@ constexpr int kInterpVars = 4;
 // and FP32 state within 27 KB (three two-wavefront workgroups per SIMD).  FP64:
 // the matrix-core interpolation reads the state from global memory, so only
 // the geometry nodes count (1e6 particles on the 32^3 box, N = 5: 554 us a
-// stage against 577 us with one task per wavefront and the state staged);
+// stage against 577 us with one task per wavefront and the state staged; N = 7,
+// 2.4e5 particles on 20^3 352 -> 201 us; elements of several hundred particles
+// lose: 585 each, N = 5 158 -> 164 us, straight elements of 3900, N = 3 375 -> 425);
 // degree 6 (8.2 KB of nodes) and the extra forces (which interpolate per lane
 // from the staged state) keep 64.
 __host__ __device__ constexpr int task_particles(int nn, int ng, bool mixed, bool forces) {

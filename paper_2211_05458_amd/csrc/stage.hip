@@ -16,6 +16,8 @@
 //  k_track       physical-space tracking (Sec. 3.2.3/3.2.4) of the queued
 //                segments: face intersection, hand-off, periodic shift, wall
 //                reflection.
+//  k_track_clip  the same by Bezier clipping of every curved face, for the
+//                segments that k_track leaves or for all of them (run_track).
 #include <type_traits>
 
 #include "fp_device.h"
