@@ -18,7 +18,7 @@ struct fp_ctx {
   int E = 0, n_geo = 0, ng = 0, N = 0, n = 0, dg_nodes = 0;
   std::vector<double> X, shift, elo, ehi, dsafe;
   std::vector<int32_t> nbr_elem, nbr_face, bstart, blist, mortar;
-  int task_tp = 64;          // particles per element task of the last sort
+  int task_tp = 64;          // particles per element task that the last sort was for
   int n_mortar = 0;
   std::vector<int8_t> bc;
   std::vector<double> Minv;
@@ -49,7 +49,7 @@ struct fp_ctx {
   unsigned long long* dep_pad = nullptr;   // largest distance of a particle outside its element box
   float* mlp_rows = nullptr;   // per-row activations for MLP gradients
   int32_t *tstart = nullptr, *qcnt = nullptr, *strag = nullptr, *trk_p = nullptr;
-  void* tasks = nullptr;
+  void *tasks32 = nullptr, *tasks64 = nullptr;
   double* trk_x = nullptr;
   uint8_t* trk_m = nullptr;
   float* trk_s = nullptr;
@@ -227,9 +227,9 @@ struct Timed {
 
 // the device counters qcnt: each stage's queue counters (stage i clears
 // stage i + 1's, the last one stage 0's, so that every step begins alike), the
-// number of element tasks, the list lengths of the final locate and of the
+// numbers of element tasks of either size, the list lengths of the final locate and of the
 // learned guess
-enum { kCntTasks = 5 * kStageCounters, kCntLocate, kCntGuess, kCounters };
+enum { kCntTasks32 = 5 * kStageCounters, kCntTasks64, kCntLocate, kCntGuess, kCounters };
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -250,7 +250,7 @@ void particle_offsets(int64_t cap, int64_t* off, size_t* total) {
 struct Layout {
   size_t X, faces, fext, cp, hE, xnode, vol, elo, ehi, nbox, dsafe, gxi, mortar, nbr_elem, nbr_face, bc, shift, bstart, blist,
       mlp_flag, mlp_h1, mlp_ctr, mlp_w, mlp_adam, mlp_order, mlp_bloss, dl_count, dl_start, dl_list, stats,
-      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tstart, tasks, qcnt,
+      sort_count, sort_start, sort_rank, sort_sums, scratch, dep, mlp_rows, tstart, tasks32, tasks64, qcnt,
       strag, trk_p, trk_x, trk_m, trk_s, mlp_guess, part[2], total;
   size_t part_bytes;
 };
@@ -299,8 +299,9 @@ Layout layout(const fp_ctx* c, int64_t cap) {
   L.dep = take((size_t)std::max<int64_t>(cap, 1) * 7 * 8 + 16);
   L.mlp_rows = take((size_t)kMlpMaxBatch * kMlpRow * 4);
   size_t pc1 = (size_t)std::max<int64_t>(cap, 1);
-  L.tstart = take(E * 4);
-  L.tasks = take((E + pc1 / kMinTaskParticles + 2) * task_bytes());
+  L.tstart = take(E * 8);
+  L.tasks32 = take((E + pc1 / 32 + 2) * task_bytes());
+  L.tasks64 = take((E + pc1 / 64 + 2) * task_bytes());
   L.qcnt = take(kCounters * 4);
   L.strag = take(pc1 * 4);
   L.trk_p = take(pc1 * 4);
@@ -445,7 +446,8 @@ void boundary_distance(fp_ctx* c) {
   }
 }
 
-// counting sort by element, then the element tasks of tp particles each
+// counting sort by element with the element tasks; the step or source that asks
+// for it works on those of tp particles
 int sort_particles(fp_ctx* c, int tp) {
   hipStream_t s = c->stream;
   if (c->np == 0) {   // nothing to bucket: no histogram is computed, so no tasks either
@@ -457,7 +459,7 @@ int sort_particles(fp_ctx* c, int tp) {
   c->sort_unclean = true;
   c->tasks_valid = false;
   HIPCHK(c, launch_sort(c->P[c->cur], c->P[1 - c->cur], c->np, c->E, c->sort_count, c->sort_start, c->sort_rank,
-                        c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks, (int64_t)c->E + c->cap / tp + 2, s));
+                        c->sort_sums, c->tstart, c->tasks32, c->tasks64, c->qcnt + kCntTasks32, s));
   c->sort_unclean = false;
   c->cur = 1 - c->cur;
   c->sorts++;
@@ -467,24 +469,18 @@ int sort_particles(fp_ctx* c, int tp) {
   return FP_OK;
 }
 
-// The stages' tasks hold tp particles; those of the last sort may have been cut
-// for another stage kernel (precision, extra forces) or by the source.  The rows
-// still lie as the sort left them.  Uncut, the stages run per lane, which is the
-// faster way for few particles (one launch, no short list of stragglers): FP64
-// steps with and without forces in turn, sorted every fourth step, us a step per
-// lane and recut: 60 000 particles in 12^3 elements 659 and 985, 150 000 in 16^3
+// Steps whose tasks are of the other size than the last sort was asked for
+// (after the source's sort, or where precision or extra forces change) use the
+// element kernel from here on, and run per lane below, which is the faster way for
+// few particles (one launch, no short list of stragglers): FP64 steps with and
+// without forces in turn, sorted every fourth step, us a step per lane and by the
+// element kernel: 60 000 particles in 12^3 elements 659 and 985, 150 000 in 16^3
 // 1278 and 1251, 200 000 in a straight 20^3 cube 778 and 868, 500 000 in 8^3 1932
 // and 1304, 1e6 in 32^3 6295 and 4689.
-constexpr int64_t kRecutMin = 1 << 18;
+constexpr int64_t kOtherTasksMin = 1 << 18;
 
-int recut_tasks(fp_ctx* c, int tp) {
-  c->tasks_valid = false;
-  HIPCHK(c, launch_recut(c->E, c->sort_start, c->sort_sums, c->tstart, tp, c->tasks, c->qcnt + kCntTasks,
-                         (int64_t)c->E + c->cap / tp + 2, c->stream));
-  c->task_tp = tp;
-  c->tasks_valid = true;
-  return FP_OK;
-}
+void* tasks_of(const fp_ctx* c, int tp) { return tp == 32 ? c->tasks32 : c->tasks64; }
+int32_t* ntask_of(const fp_ctx* c, int tp) { return c->qcnt + (tp == 32 ? kCntTasks32 : kCntTasks64); }
 
 int sync_bound(fp_ctx* c) {
   if (!c->bound || c->cur == 0 || c->np == 0) return FP_OK;
@@ -763,7 +759,8 @@ int fp_bind_workspace(fp_ctx* c, void* dev, size_t bytes) {
   c->dep_buf = (double*)(b + L.dep);
   c->mlp_rows = (float*)(b + L.mlp_rows);
   c->tstart = (int32_t*)(b + L.tstart);
-  c->tasks = (void*)(b + L.tasks);
+  c->tasks32 = (void*)(b + L.tasks32);
+  c->tasks64 = (void*)(b + L.tasks64);
   c->qcnt = (int32_t*)(b + L.qcnt);
   c->strag = (int32_t*)(b + L.strag);
   c->trk_p = (int32_t*)(b + L.trk_p);
@@ -924,21 +921,18 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
   hipStream_t s = c->stream;
   const int tp = task_particles(c->n, c->ng, o->precision == 1, o->forces != 0);
   // stage 0 finds its counters cleared by the last step's last stage
-  if (c->stage_unclean) HIPCHK(c, launch_clear_i32(c->qcnt, kCntTasks, s));
+  if (c->stage_unclean) HIPCHK(c, launch_clear_i32(c->qcnt, kCntTasks32, s));
   c->stage_unclean = true;
   for (int st = 0; st < n_steps; ++st) {
     if (o->sort_every < 0 || (o->sort_every > 0 && (c->steps_done % o->sort_every) == 0)) {
       // a sort since the particles last moved (the shape-kernel source sorts
       // after locating them) already holds the tasks of this step
-      if (!(c->sorted_fresh && c->tasks_valid && c->task_tp == tp)) {
+      if (!(c->sorted_fresh && c->tasks_valid)) {
         Timed tm(c, 0);
         int rc = sort_particles(c, tp);
         if (rc) return rc;
       }
-    } else if (c->tasks_valid && c->task_tp != tp && c->np >= kRecutMin) {
-      Timed tm(c, 0);
-      int rc = recut_tasks(c, tp);
-      if (rc) return rc;
+      c->task_tp = tp;
     }
     c->sorted_fresh = false;
     for (int i = 0; i < S; ++i) {
@@ -959,9 +953,9 @@ int fp_step(fp_ctx* c, double dt, int32_t n_steps, const fp_step_opts* o) {
       Lc.n = c->np;
       Lc.mixed = o->precision;
       Lc.mlp = sp.use_mlp;
-      Lc.tasks = c->tasks_valid ? c->tasks : nullptr;
-      Lc.task_tp = c->task_tp;
-      Lc.ntask = c->qcnt + kCntTasks;
+      Lc.tasks = c->tasks_valid && (c->task_tp == tp || c->np >= kOtherTasksMin) ? tasks_of(c, tp) : nullptr;
+      Lc.task_tp = tp;
+      Lc.ntask = ntask_of(c, tp);
       Lc.counters = c->qcnt + kStageCounters * i;
       Lc.next_counters = c->qcnt + kStageCounters * ((i + 1) % S);
       Lc.guess_count = c->qcnt + kCntGuess;
@@ -1007,8 +1001,8 @@ static hipError_t finalize(fp_ctx* c, hipStream_t s) {
   const int warm = c->xi_warm ? 1 : 0;
   const Particles& P = c->P[c->cur];
   if (c->tasks_valid)
-    return launch_finalize_elem(c->mv, P, c->tasks, c->qcnt + kCntTasks, c->task_tp, c->np, warm, c->qcnt + kCntLocate, c->strag,
-                                c->stats, s);
+    return launch_finalize_elem(c->mv, P, tasks_of(c, c->task_tp), ntask_of(c, c->task_tp), c->task_tp, c->np, warm,
+                                c->qcnt + kCntLocate, c->strag, c->stats, s);
   return launch_finalize(c->mv, P, c->np, nullptr, nullptr, warm, c->stats, s);
 }
 
@@ -1079,7 +1073,8 @@ int fp_deposit_source(fp_ctx* c, void* S, fp_dtype dt, int32_t kind, double radi
                                      c->node_pad, c->dep_buf, c->sort_start, c->dep_pad,
                                      c->count_pairs ? c->stats + ST_DEP_PAIRS * kStatSlots : nullptr, c->dl_valid ? c->dl_start : nullptr,
                                      c->dl_list, c->dl_pad, c->rl_buf, c->rl_cap,
-                                     c->tasks_valid ? c->tasks : nullptr, c->qcnt + kCntTasks, c->task_tp, ev, c->stream));
+                                     c->tasks_valid ? tasks_of(c, c->task_tp) : nullptr, ntask_of(c, c->task_tp), c->task_tp, ev,
+                                     c->stream));
     }
     if (c->timing && ev[0] && ev[1] && ev[2] && ev[3]) {
       c->recs.push_back({7, ev[0], ev[1]});

@@ -148,8 +148,6 @@ __host__ __device__ constexpr int task_particles(int nn, int ng, bool mixed, boo
   if (!mixed) return (!forces && ng < 7) ? 32 : 64;
   return 4 * (ng * ng * ng * 3 * 8 + kInterpVars * nn * nn * nn * 4) <= 27 * 1024 ? 32 : 64;
 }
-constexpr int kMinTaskParticles = 32;
-
 // one element task of the stage kernels: particles p0 .. p0 + cnt of element e
 struct Task { int32_t e, p0, cnt, pad; };
 

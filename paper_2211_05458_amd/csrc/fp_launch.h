@@ -75,14 +75,12 @@ inline size_t deposit_reuse_bytes(int E, int32_t cap) {
 hipError_t launch_dep_lists(const MeshView& m, double R, const double* period, double pad, int pass,
                             int32_t* count, const int32_t* start, int32_t* list, hipStream_t s);
 constexpr int kDepListPerElem = 256;   // workspace budget of candidate-list entries per element
-// counting sort of src into dst and the element tasks of tp particles each;
-// count (E + 1 entries) is zero before and after
+// counting sort of src into dst and the element tasks of 32 and of 64 particles
+// (ntask[0], ntask[1] of them; tstart holds 2 E values); count (E + 1 entries) is
+// zero before and after
 hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count, int32_t* start,
-                       int32_t* rank, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
-                       int64_t max_tasks, hipStream_t s);
-// the last sort's buckets (its starts) cut into tasks of tp particles
-hipError_t launch_recut(int E, int32_t* start, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
-                        int64_t max_tasks, hipStream_t s);
+                       int32_t* rank, int32_t* sums, int32_t* tstart, void* tasks32, void* tasks64, int32_t* ntask,
+                       hipStream_t s);
 hipError_t launch_clear_i32(int32_t* a, int64_t n, hipStream_t s);
 hipError_t launch_copy_particles(const Particles& S, const Particles& D, int64_t n, hipStream_t s);
 

@@ -4,7 +4,10 @@
 // clears the histogram for the next sort, then a scatter of every SoA field, in
 // which the first particle of each task writes it (a thread of the scan would
 // write the tasks of its buckets one after the other: 1e6 particles in 8
-// elements 1640 us a sort instead of 267, in 16^3 103 instead of 88).
+// elements 1640 us a sort instead of 267, in 16^3 103 instead of 88).  The tasks
+// are cut both ways, 32 and 64 particles: the steps that follow a sort may need
+// either (precision, extra forces, the source), one after the other or in a
+// captured graph.
 // Launches of a few microseconds each are what a sort of few particles costs:
 // clear, histogram, two three-launch scans, task count, task fill and scatter
 // were 11 of them (46 us for 1e4 particles); one scan of bucket starts and task
@@ -104,8 +107,8 @@ __global__ void k_scan_add(int32_t* out, int64_t n, const int32_t* sums) {
 __global__ __launch_bounds__(256) void k_sort_scatter(Particles S, Particles D, int64_t n, int E,
                                                       const int32_t* __restrict__ start,
                                                       const int32_t* __restrict__ rank,
-                                                      const int32_t* __restrict__ tstart, int tp,
-                                                      Task* __restrict__ tasks, int64_t max_tasks) {
+                                                      const int2* __restrict__ tstart, Task* __restrict__ tasks32,
+                                                      Task* __restrict__ tasks64) {
   int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
   int8_t st = S.status[p];
@@ -113,9 +116,11 @@ __global__ __launch_bounds__(256) void k_sort_scatter(Particles S, Particles D, 
   int key = st == ACTIVE ? e : E;
   const int r = rank[p];
   int64_t q = (int64_t)start[key] + r;
-  if (key < E && r % tp == 0) {
-    const int64_t t = (int64_t)tstart[key] + r / tp;
-    if (t < max_tasks) tasks[t] = Task{key, (int32_t)q, min(tp, start[key + 1] - (int32_t)q), 0};
+  if (key < E && r % 32 == 0) {
+    const int2 t = tstart[key];
+    const int left = start[key + 1] - (int32_t)q;
+    tasks32[t.x + r / 32] = Task{key, (int32_t)q, min(32, left), 0};
+    if (r % 64 == 0) tasks64[t.y + r / 64] = Task{key, (int32_t)q, min(64, left), 0};
   }
   const int64_t cs = S.cap, cd = D.cap;
 #pragma unroll
@@ -143,144 +148,98 @@ hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* sums, h
 
 constexpr int kScanPer = 16, kScanTile = 256 * kScanPer;   // buckets per thread and per workgroup
 
-// exclusive prefix over the workgroup's 256 threads of two sums at once
-__device__ __forceinline__ void block_scan2(int& a, int& b, int* ta, int* tb) {
-  __shared__ int sa[4], sb[4];
+// what the scan adds up: particles, tasks of 32 and tasks of 64
+struct SortSum { int p, t32, t64; };
+
+__device__ __forceinline__ SortSum operator+(SortSum a, SortSum b) { return {a.p + b.p, a.t32 + b.t32, a.t64 + b.t64}; }
+
+// bucket e of c particles (bucket E, the inactive particles, has no tasks)
+__device__ __forceinline__ SortSum bucket_sum(int c, bool element) {
+  return {c, element ? (c + 31) / 32 : 0, element ? (c + 63) / 64 : 0};
+}
+
+// exclusive prefix over the workgroup's 256 threads, and the sum
+__device__ __forceinline__ SortSum block_scan(SortSum a, SortSum* total) {
+  __shared__ SortSum sums[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int x = a, y = b;
+  SortSum x = a;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(x, o, 64), v = __shfl_up(y, o, 64);
-    if (lane >= o) { x += u; y += v; }
+    const SortSum u{__shfl_up(x.p, o, 64), __shfl_up(x.t32, o, 64), __shfl_up(x.t64, o, 64)};
+    if (lane >= o) x = x + u;
   }
-  if (lane == 63) { sa[wave] = x; sb[wave] = y; }
+  if (lane == 63) sums[wave] = x;
   __syncthreads();
-  int pa = 0, pb = 0;
-  *ta = *tb = 0;
+  SortSum before{0, 0, 0};
+  *total = before;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    if (w < wave) { pa += sa[w]; pb += sb[w]; }
-    *ta += sa[w];
-    *tb += sb[w];
+    if (w < wave) before = before + sums[w];
+    *total = *total + sums[w];
   }
   __syncthreads();
-  a = pa + x - a;
-  b = pb + y - b;
+  return {before.p + x.p - a.p, before.t32 + x.t32 - a.t32, before.t64 + x.t64 - a.t64};
 }
 
-__device__ __forceinline__ int tasks_of(int count, int tp) { return (count + tp - 1) / tp; }
-
-// RECUT: the sort is done, its histogram cleared; a bucket's size from the starts
-// (bucket E is of no interest)
-template <bool RECUT>
-__device__ __forceinline__ int bucket_size(const int32_t* __restrict__ count, const int32_t* __restrict__ start,
-                                           int64_t e, int E) {
-  if (RECUT) return e < E ? start[e + 1] - start[e] : 0;
-  return e <= E ? count[e] : 0;
-}
-
-// sums of each tile of buckets: particles and element tasks (bucket E, the
-// inactive particles, has no tasks)
-template <bool RECUT>
-__global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ count,
-                                                   const int32_t* __restrict__ start, int E, int tp, int32_t* sums) {
+// sums of each tile of buckets
+__global__ __launch_bounds__(256) void k_sort_sums(const int32_t* __restrict__ count, int E, SortSum* sums) {
   const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
-  int a = 0, b = 0, ta, tb;
+  SortSum a{0, 0, 0}, total;
   for (int k = 0; k < kScanPer; ++k) {
     const int64_t e = b0 + k * 256 + threadIdx.x;
-    const int c = bucket_size<RECUT>(count, start, e, E);
-    a += c;
-    if (e < E) b += tasks_of(c, tp);
+    if (e <= E) a = a + bucket_sum(count[e], e < E);
   }
-  block_scan2(a, b, &ta, &tb);
-  if (threadIdx.x == 0) {
-    sums[2 * blockIdx.x] = ta;
-    sums[2 * blockIdx.x + 1] = tb;
-  }
+  block_scan(a, &total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// starts of the buckets' particles and of their tasks of at most tp particles,
-// and the number of tasks; the histogram is cleared.  sums: every tile's sums
-// (the workgroup adds those before its own: a few hundred values for the largest
-// meshes).  RECUT: only the task starts and the number of tasks.
-template <bool RECUT>
+// starts of the buckets' particles and of their tasks of either size, and the
+// numbers of tasks; the histogram is cleared.  sums: every tile's sums (the
+// workgroup adds those before its own: a few hundred values for the largest
+// meshes).
 __global__ __launch_bounds__(256) void k_sort_scan(int32_t* __restrict__ count, int32_t* __restrict__ start, int E,
-                                                   int tp, const int32_t* __restrict__ sums,
-                                                   int32_t* __restrict__ tstart, int32_t* ntask) {
-  int before = 0, tbefore = 0, ta, tb;
+                                                   const SortSum* __restrict__ sums, int2* __restrict__ tstart,
+                                                   int32_t* ntask) {
+  SortSum before{0, 0, 0}, total;
   if (blockIdx.x > 0) {
-    int a = 0, b = 0;
-    for (int t = threadIdx.x; t < (int)blockIdx.x; t += 256) {
-      a += sums[2 * t];
-      b += sums[2 * t + 1];
-    }
-    block_scan2(a, b, &before, &tbefore);
+    SortSum a{0, 0, 0};
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += 256) a = a + sums[t];
+    block_scan(a, &before);
   }
   const int64_t e0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-  int c[kScanPer], a = 0, b = 0;
+  int c[kScanPer];
+  SortSum a{0, 0, 0};
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
-    c[k] = bucket_size<RECUT>(count, start, e0 + k, E);
-    a += c[k];
-    if (e0 + k < E) b += tasks_of(c[k], tp);
+    c[k] = e0 + k <= E ? count[e0 + k] : 0;
+    a = a + bucket_sum(c[k], e0 + k < E);
   }
-  block_scan2(a, b, &ta, &tb);
-  a += before;
-  b += tbefore;
+  a = before + block_scan(a, &total);
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
     const int64_t e = e0 + k;
     if (e > E) break;
-    if (!RECUT) {
-      start[e] = a;
-      count[e] = 0;
-    }
+    start[e] = a.p;
+    count[e] = 0;
     if (e < E) {
-      tstart[e] = b;
-      b += tasks_of(c[k], tp);
+      tstart[e] = make_int2(a.t32, a.t64);
     } else {
-      *ntask = b;
+      ntask[0] = a.t32;
+      ntask[1] = a.t64;
     }
-    a += c[k];
+    a = a + bucket_sum(c[k], e < E);
   }
 }
 
 hipError_t launch_sort(const Particles& src, const Particles& dst, int64_t n, int E, int32_t* count, int32_t* start,
-                       int32_t* rank, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
-                       int64_t max_tasks, hipStream_t s) {
+                       int32_t* rank, int32_t* sums, int32_t* tstart, void* tasks32, void* tasks64, int32_t* ntask,
+                       hipStream_t s) {
   if (n == 0) return hipSuccess;
   const dim3 g((unsigned)((n + 255) / 256)), tiles((unsigned)((E + kScanTile) / kScanTile));   // E + 1 buckets
   k_sort_hist<<<g, 256, 0, s>>>(src.status, src.elem, n, E, count, rank);
-  if (tiles.x > 1) k_sort_sums<false><<<tiles, 256, 0, s>>>(count, start, E, tp, sums);
-  k_sort_scan<false><<<tiles, 256, 0, s>>>(count, start, E, tp, sums, tstart, ntask);
-  k_sort_scatter<<<g, 256, 0, s>>>(src, dst, n, E, start, rank, tstart, tp, (Task*)tasks, max_tasks);
-  return hipGetLastError();
-}
-
-// tasks of another size from the bucket starts: each finds its element in the
-// task starts
-__global__ __launch_bounds__(256) void k_task_fill(const int32_t* __restrict__ start,
-                                                   const int32_t* __restrict__ tstart, int E, int tp,
-                                                   const int32_t* __restrict__ ntask, Task* __restrict__ tasks,
-                                                   int64_t max_tasks) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= max_tasks || i >= *ntask) return;
-  int lo = 0, hi = E;   // the last element whose first task is at most i: the only one of them with tasks
-  while (hi - lo > 1) {
-    const int mid = lo + (hi - lo) / 2;
-    if (tstart[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  const int p0 = start[lo] + ((int)i - tstart[lo]) * tp;
-  tasks[i] = Task{lo, p0, min(tp, start[lo + 1] - p0), 0};
-}
-
-hipError_t launch_recut(int E, int32_t* start, int32_t* sums, int32_t* tstart, int tp, void* tasks, int32_t* ntask,
-                        int64_t max_tasks, hipStream_t s) {
-  const dim3 tiles((unsigned)((E + kScanTile) / kScanTile)), g((unsigned)((max_tasks + 255) / 256));
-  if (tiles.x > 1) k_sort_sums<true><<<tiles, 256, 0, s>>>(nullptr, start, E, tp, sums);
-  k_sort_scan<true><<<tiles, 256, 0, s>>>(nullptr, start, E, tp, sums, tstart, ntask);
-  k_task_fill<<<g, 256, 0, s>>>(start, tstart, E, tp, ntask, (Task*)tasks, max_tasks);
+  if (tiles.x > 1) k_sort_sums<<<tiles, 256, 0, s>>>(count, E, (SortSum*)sums);
+  k_sort_scan<<<tiles, 256, 0, s>>>(count, start, E, (const SortSum*)sums, (int2*)tstart, ntask);
+  k_sort_scatter<<<g, 256, 0, s>>>(src, dst, n, E, start, rank, (const int2*)tstart, (Task*)tasks32, (Task*)tasks64);
   return hipGetLastError();
 }
 

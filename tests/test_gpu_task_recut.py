@@ -1,6 +1,7 @@
-"""Element tasks cut for another stage kernel than the one that runs: the shape
+"""Element tasks of another size than the last sort was for: the shape
 source sorts where the steps do not, steps with and without the extra forces
-take turns between two sorts, the fluid state changes precision.
+take turns between two sorts, the fluid state changes precision, a captured step
+is replayed between sorts for the other size.
 
 Bar: from 2^18 particles on every stage runs the element kernel, below it the
 stages whose tasks fit do; the FP64 states are bitwise those of steps that never
@@ -71,3 +72,48 @@ def test_state_changes_precision_between_sorts():
     assert g.timing()["stage_elem"][0] == 4 * (5 if w.rk == 0 else 3)
     st = g.stats()
     assert st["lost"] == 0 and st["sorts"] == 1
+
+
+@pytest.mark.parametrize("forces", [0, 15])
+def test_captured_step_after_a_sort_for_other_tasks(forces):
+    """A captured step that does not sort runs on the last sort's tasks.  Between
+    its replays steps with the other setting of the extra forces sort."""
+    import torch
+    n = 4000                                  # about 62 particles an element: tasks of 32 and of 64 differ
+    w = W.curved_box(cells=4, N=3, n_particles=n, seed=54)
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2211_05458_amd.lib import FlexiPart
+    _, nb = FlexiPart.particle_block_layout(n)
+    stream = torch.cuda.Stream()
+
+    def step(g, f, sort):
+        g.step(w.dt, 1, rk=w.rk, drag=w.drag, forces=f, gravity=GRAVITY, sort_every=sort)
+
+    def start():
+        g = FlexiPart(w.mesh, w.N, n)
+        g.set_fluid_state(w.U)
+        g.bind_particles(torch.zeros(nb, dtype=torch.uint8, device="cuda"), n)
+        g.push(w.x, w.v * 10.0, w.d, w.elem_hint)
+        step(g, forces, 1)
+        return g
+    with torch.cuda.stream(stream):
+        a, b = start(), start()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            step(a, forces, 0)
+        for _ in range(3):
+            graph.replay()
+            step(b, forces, 0)
+            stream.synchronize()
+            torch.cuda.synchronize()
+            step(a, 15 - forces, 1)
+            step(b, 15 - forces, 1)
+            stream.synchronize()
+        graph.replay()
+        step(b, forces, 0)
+        torch.cuda.synchronize()
+        ra, rb = a.read(), b.read()
+    for k in ra:
+        np.testing.assert_array_equal(ra[k], rb[k])
