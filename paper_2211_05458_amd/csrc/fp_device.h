@@ -924,17 +924,19 @@ __device__ inline void face_bounds(const double* __restrict__ cp, const FaceRec&
   X.cn = (float)(1.03 * sqrt(cc[0]) + fl);
   X.c1 = (float)(1.03 * sqrt(cc[1]) + fl);
   X.c2f = (float)(1.03 * sqrt(cc[2]) + fl);
-  // smallest stretch of the face's parameters on a lattice
+  // the smallest stretch of the face's parameters is at least (1 - eps) / |B|;
+  // where that does not settle it, on a lattice
+  X.hard = 0;
+  const double b2 = dot3(B[0], B[0]) + dot3(B[1], B[1]), low = fmax(0.0, 1.0 - eps);
+  if (F.type != FACE_CURVED || (X.inv1e > 0.0f && c2 * b2 < kMaxBend * kMaxBend * low * low)) return;
   double g2 = 1e300;
-  for (int k = 0; k < 25 && F.type == FACE_CURVED; ++k) {
+  for (int k = 0; k < 25; ++k) {
     double p[3], pu[3], pv[3];
     face_eval<NG>(cp, -1.0 + 0.5 * (k % 5), -1.0 + 0.5 * (k / 5), p, pu, pv);
     const double uu = dot3(pu, pu), uv = dot3(pu, pv), vv = dot3(pv, pv);
     g2 = fmin(g2, 0.5 * (uu + vv) - sqrt(0.25 * (uu - vv) * (uu - vv) + uv * uv));
   }
-  X.hard = 0;
-  if (F.type == FACE_CURVED && !(X.inv1e > 0.0f && c2 < kMaxBend * kMaxBend * g2))
-    X.hard = c2 < kFoldBend * kFoldBend * g2 ? 1 : 2;
+  if (!(X.inv1e > 0.0f && c2 < kMaxBend * kMaxBend * g2)) X.hard = c2 < kFoldBend * kFoldBend * g2 ? 1 : 2;
 }
 
 // how the face parameters of the neighbour across face f of element e follow
